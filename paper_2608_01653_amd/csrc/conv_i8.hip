@@ -1978,12 +1978,19 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_rr32_kernel(const ConvArg
         __syncthreads();
     }
     if constexpr (PASS == 0) {
-        // one atomic per wave and run (a run is one sample); the running maximum
-        // only grows, so a wave that does not exceed the published value skips it
+        // one atomic per block and run (a run is one sample; the patch buffers
+        // are free after the last tile's barrier); the running maximum only
+        // grows, so a block that does not exceed the published value skips it
         const float m = wave_max(wave_m);
-        if (lane == 0 && m > __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + nb),
-                                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
-            atomic_max_nonneg(a.next_absmax + nb, m);
+        float *red = reinterpret_cast<float *>(s_patch[0]);
+        if (lane == 0) red[wave] = m;
+        __syncthreads();
+        if (tid == 0) {
+            const float bm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+            if (bm > __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + nb),
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                atomic_max_nonneg(a.next_absmax + nb, bm);
+        }
     }
 }
 
@@ -2214,9 +2221,26 @@ inline int rr32_kron_pass(const ConvArgs &a) {
     return -1;
 }
 
-#ifndef HATQ_RR32_TH
-#define HATQ_RR32_TH 16
-#endif
+// Output rows per tile (four waves, TH / 4 rows each) and tiles per block.  The
+// kernel is bound by the vector ALU, so what counts is that every CU has the
+// same rows to do.  One tile per block leaves the balance to the hardware's
+// dispatch (the XCDs hold different clocks under this load, so an even split
+// into resident blocks ends unevenly): batch 16 of 1024 x 1024, absmax 343 ->
+// 325 us, codes 449 -> 436, integer 767 -> 677.  Fewer tiles of 16 rows than
+// the blocks that fit the chip leave CUs idle: smaller tiles then, although
+// each block stages the weights anew.  Measured absmax + codes at 4 / 8 / 16
+// rows: 192 tiles (512 x 768) 32 / 41 / 55 us, 384 tiles 54 / 51 / 68, 768 tiles
+// 95 / 90 / 91, 1376 tiles 159 / 144 / 155, 2560 tiles 280 / 251 / 251, 8192
+// tiles 865 / 782 / 765.  (One block used to walk at least four 16-row tiles:
+// 172 us at 192 tiles.)
+inline int rr32_rows(const ConvArgs &a) {
+    const int64_t t16 = (int64_t)a.n * ((a.gh + 15) / 16) * ((a.gw + kRr32W - 1) / kRr32W);
+    return t16 < 320 ? 4 : t16 < 2048 ? 8 : 16;
+}
+// Order 192 (two blocks per CU): two tiles per block on the largest launches,
+// so the next patch is fetched behind the longer arithmetic (8192 tiles: absmax
+// 691 -> 642 us, codes 729 -> 719).
+inline int rr32_run(const ConvArgs &a, int ord) { return ord == 192 && rr32_rows(a) == 16 ? 2 : 1; }
 #ifndef HATQ_RR32_MINB
 #define HATQ_RR32_MINB 4
 #endif
@@ -2239,9 +2263,7 @@ hipError_t launch_rr32(const ConvArgs &a, hipStream_t st) {
     // every byte offset of the input fits the 32-bit buffer range
     if ((int64_t)b.n * b.h * b.w * 3 >= ((int64_t)1 << 31) - 64) return hipErrorInvalidValue;
     const int64_t per = (int64_t)b.tiles_h * b.tiles_w;
-    const int64_t slots = MINB * (int64_t)persistent_blocks();   // resident blocks (0 if unknown)
-    int64_t run = slots > 0 ? (b.n * per + slots - 1) / slots : kRowRunMin;
-    run = run < kRowRunMin ? kRowRunMin : run > kRowRunMax ? kRowRunMax : run;
+    const int64_t run = rr32_run(b, ORD);
     b.run_tiles = (int32_t)run;
     const int64_t blocks = (int64_t)b.n * ((per + run - 1) / run);
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
@@ -3313,18 +3335,23 @@ hipError_t conv_part_pipe_other(const ConvArgs &a, hipStream_t st) {
 hipError_t conv_part_rowrun3(const ConvArgs &a, hipStream_t st) { return launch_rowrun_n<3>(a, st); }
 #endif
 #if HATQ_PART(13)
-hipError_t conv_part_rr32(const ConvArgs &a, int pass, hipStream_t st) {
+template <int TH>
+static hipError_t rr32_th(const ConvArgs &a, int pass, hipStream_t st) {
     // 3, 4: the absmax and codes passes with the order 192 on both sides
-    if (pass == 3) return launch_rr32<HATQ_RR32_TH, 3, 0, false, HATQ_RR32_MINB_KRON, 192>(a, st);
-    if (pass == 4) return launch_rr32<HATQ_RR32_TH, 3, 1, false, HATQ_RR32_MINB_KRON, 192>(a, st);
+    if (pass == 3) return launch_rr32<TH, 3, 0, false, HATQ_RR32_MINB_KRON, 192>(a, st);
+    if (pass == 4) return launch_rr32<TH, 3, 1, false, HATQ_RR32_MINB_KRON, 192>(a, st);
     if (pass == 2)
-        return a.paired ? launch_rr32<HATQ_RR32_TH, 3, 2, true, HATQ_RR32_MINB_INT>(a, st)
-                        : launch_rr32<HATQ_RR32_TH, 3, 2, false, HATQ_RR32_MINB_INT>(a, st);
+        return a.paired ? launch_rr32<TH, 3, 2, true, HATQ_RR32_MINB_INT>(a, st)
+                        : launch_rr32<TH, 3, 2, false, HATQ_RR32_MINB_INT>(a, st);
     if (a.paired)
-        return pass == 0 ? launch_rr32<HATQ_RR32_TH, 3, 0, true, HATQ_RR32_MINB>(a, st)
-                         : launch_rr32<HATQ_RR32_TH, 3, 1, true, HATQ_RR32_MINB>(a, st);
-    return pass == 0 ? launch_rr32<HATQ_RR32_TH, 3, 0, false, HATQ_RR32_MINB>(a, st)
-                     : launch_rr32<HATQ_RR32_TH, 3, 1, false, HATQ_RR32_MINB>(a, st);
+        return pass == 0 ? launch_rr32<TH, 3, 0, true, HATQ_RR32_MINB>(a, st)
+                         : launch_rr32<TH, 3, 1, true, HATQ_RR32_MINB>(a, st);
+    return pass == 0 ? launch_rr32<TH, 3, 0, false, HATQ_RR32_MINB>(a, st)
+                     : launch_rr32<TH, 3, 1, false, HATQ_RR32_MINB>(a, st);
+}
+hipError_t conv_part_rr32(const ConvArgs &a, int pass, hipStream_t st) {
+    const int th = rr32_rows(a);
+    return th == 4 ? rr32_th<4>(a, pass, st) : th == 8 ? rr32_th<8>(a, pass, st) : rr32_th<16>(a, pass, st);
 }
 #endif
 #if HATQ_PART(7)

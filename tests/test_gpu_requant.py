@@ -241,3 +241,38 @@ def test_requant_small_cin_tiles(orc, c):
     assert_codes(host(yqp), qz, exact=True, what="paired small-cin codes")
     assert np.all(np.abs(host(sqp).astype(np.float64) - s_ref) <= tol)
     assert_codes(host(yqp), q_ref, what="paired small-cin codes vs the oracle's composition")
+
+
+# The 32 x 32 tiles have 4, 8 or 16 output rows by the size of the launch: batches
+# on both sides of each limit (319, 320, 2047 and 2048 tiles of 16 rows), ragged in
+# both directions, against the first samples alone (4 rows, compared with the
+# oracle above) and against the activation kernel on the fp32 output, bit for bit.
+@pytest.mark.parametrize("n,gh", [(319, 11), (160, 19), (2047, 9), (1024, 19)])
+@pytest.mark.parametrize("hb", [64, 192])
+def test_requant_small_cin_rows_per_tile(n, gh, hb):
+    rng = np.random.default_rng(84)
+    wt, b = synth.layer_params(rng, 3, 192, 5)
+    layer = hatq.hatq_prepare_weights(hatq.desc(3, 192, 5, 2, 2, hb), "WH", dev(wt), dev(b))
+    x = torch.rand((n, 2 * gh - 1, 13, 3), device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    xq, sx = hatq.hatq_fwht_quant_act(x, 1)
+
+    def passes(q, s):
+        m = torch.full((q.shape[0],), -1.0, device="cuda")
+        hatq.hatq_conv_int8(layer, q, s, hatq.HATQ_OUT_F32, next_hblock=hb, next_absmax=m, absmax_only=True)
+        yq, sq = hatq.hatq_conv_int8_requant(layer, q, s, hb, next_absmax=m)
+        out = [m, yq, sq]
+        if hb == 64:
+            t, _ = hatq.hatq_int_transition_params(layer, 0.004, 0.02, 64)
+            out += [hatq.hatq_conv_int8_int_transition(layer, q, 64, t, paired=p) for p in (False, True)]
+        return out
+
+    got = passes(xq, sx)
+    alone = passes(xq[:5].contiguous(), sx[:5].contiguous())
+    for g, a in zip(got, alone):
+        assert torch.equal(g[:5], a)
+    m = torch.full((n,), -1.0, device="cuda")
+    y = hatq.hatq_conv_int8(layer, xq, sx, hatq.HATQ_OUT_F32, next_hblock=hb, next_absmax=m)
+    q, s = hatq.hatq_fwht_quant_act(y, hb, absmax=m)
+    assert torch.equal(got[0], m) and torch.equal(got[1], q) and torch.equal(got[2], s)
+    if hb == 64:
+        assert torch.equal(got[3], got[4])   # B_next B_Cout = b I: the same codes
