@@ -254,13 +254,15 @@ int32_t conv_launches(const hatq_weights *W, const int8_t *xq, const float *sx, 
             }
         a.nksteps = small ? W->pack_stride / 64 : a.ntaps * (W->cin_pad / 64);
         a.M = (int64_t)n * a.gh * a.gw;
-        return hip_status(hatq::launch_conv(a, true, st));
+        return hip_status(hatq::launch_conv(&a, 1, st));
     }
     // transposed, stride 2: four phases
-    bool first = true;
+    hatq::ConvArgs phases[hatq::kMaxPhases];
+    int nph = 0;
     for (int ph = 0; ph < 2; ++ph)
         for (int pw = 0; pw < 2; ++pw) {
-            hatq::ConvArgs b = a;
+            hatq::ConvArgs &b = phases[nph];
+            b = a;
             b.gh = (ho - ph + 1) / 2;
             b.gw = (wo - pw + 1) / 2;
             if (b.gh <= 0 || b.gw <= 0) continue;
@@ -285,11 +287,9 @@ int32_t conv_launches(const hatq_weights *W, const int8_t *xq, const float *sx, 
             b.nksteps = nt * (W->cin_pad / 64);
             b.M = (int64_t)n * b.gh * b.gw;
             if (nt == 0) continue;   // cannot happen for k >= 2
-            // next_absmax is cleared by the first phase and accumulated by the rest
-            if (hatq::launch_conv(b, first, st) != hipSuccess) return HATQ_EHIP;
-            first = false;
+            ++nph;
         }
-    return HATQ_OK;
+    return nph ? hip_status(hatq::launch_conv(phases, nph, st)) : HATQ_OK;
 }
 
 }  // namespace

@@ -1032,7 +1032,11 @@ struct Epilogue {
             }
         };
         if (f32 && !serial) load_factors();
-        const bool blk_full = t.n0 + 64 * k + 64 <= a.cout;
+        // (the channel count is read once and the masks take no branch: with the
+        // argument read behind a lane's own condition, the compiler dropped the
+        // masked values of partly valid groups in one kernel)
+        const int cout = a.cout;
+        const bool blk_full = t.n0 + 64 * k + 64 <= cout;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             // The requantizing and absmax-only variants (the small-cin layer's
@@ -1079,7 +1083,7 @@ struct Epilogue {
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
                                 const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                                const bool in = valid[i] && ch < a.cout;
+                                const bool in = valid[i] & (ch < cout);
                                 mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
                             }
                     }
@@ -1111,7 +1115,7 @@ struct Epilogue {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                        const bool in = all || (valid[i] && ch < a.cout);
+                        const bool in = all | (valid[i] & (ch < cout));
                         mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
                     }
                 wave_m = fmaxf(wave_m, mm);
@@ -1124,7 +1128,7 @@ struct Epilogue {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                            if (!valid[i] || ch >= a.cout) v[4 * jj + r] = 0.0f;
+                            if (!valid[i] | (ch >= cout)) v[4 * jj + r] = 0.0f;
                         }
                 }
                 if (i8) {
@@ -3171,6 +3175,346 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
     wait_vmcnt<0>();   // no DMA may still be writing LDS when the block ends
 }
 
+// ---------------------------------------------------------------------------
+// Small launches (cin_p % 64 == 0): a tile of FM x 16 output points by 64 output
+// columns per block, and the K-steps (taps x chunks) divided over the KS waves of
+// the block.  A launch of few tiles leaves most CUs idle on the 8 x 32 x 192
+// tiles of the other kernels, whatever its size (a 5x5 layer's 75 K-steps in a
+// row take 41 us); here it has 12 (FM = 4) or 6 (FM = 8) times as many blocks,
+// each with 1/KS of the steps in a row.  Every wave accumulates the whole tile
+// over its own steps: the weights of a step are read by one wave only, straight
+// from L2 into registers (fragment order, two steps ahead), so the main loop has
+// no LDS ring and no barrier but one or two per chunk; the partial sums (whole
+// numbers, so in any order) meet in LDS at the end, and wave w finishes the
+// output rows w, w + KS, ...
+//
+// The input window of the tile is kept per 64-channel chunk in nbuf LDS buffers
+// (all chunks where they fit, else refilled chunk by chunk).  Window records are
+// 64 bytes (one pixel of one chunk), chunk-swizzled like the operand tiles.
+// Stride 2 keeps the even columns of a window row before the odd ones, so a
+// fragment's 16 output columns are 16 consecutive records; a row takes RR
+// records, and RR * SA is a multiple of 8, so the rows of a fragment differ by a
+// multiple of 512 bytes (the same swizzle) and one address per step serves all
+// FM fragments with immediate offsets.
+//
+// SA = 1 also takes the four phases of a stride-2 transposed convolution in one
+// launch (a block belongs to one phase).
+// ---------------------------------------------------------------------------
+struct WinGeom {
+    int32_t h0, w0;       // input row and column of the window's first record: gi0 * SA + h0, gj0 * SA + w0
+    int32_t rows, cols;   // window rows and columns in use
+    // tap t = i * nkw + j: window position (r0 + i * ri, c0 + j * cj), weight tap t0 + i * ti + j * tj
+    int32_t nkw, r0, ri, c0, cj, t0, ti, tj;
+    int32_t nbuf;         // chunk buffers of the window in LDS
+};
+template <int NPH>
+struct WinArgs {
+    ConvArgs p[NPH];
+    WinGeom g[NPH];
+    int32_t nph;
+};
+template <int SA>
+struct WinShape {
+    static constexpr int NPH = SA == 2 ? 1 : kMaxPhases;
+    static constexpr int TW = 16, HCC = 18;                  // HCC: window columns of one parity (SA = 2)
+    static constexpr int RR = SA == 2 ? 2 * HCC : 24;        // records per window row: spans up to 6 (9)
+    static constexpr int ROWB = RR * 64, FROW = SA * ROWB;   // bytes per window row, per output row
+    static constexpr int TAB = 256;                          // K-steps of a launch, at most
+    static constexpr int BASE = TAB * 8 + 512;               // LDS: step table, column factors, window
+    static_assert(FROW % 512 == 0 && BASE % 512 == 0, "swizzle bits");
+    // 1 KB blocks of one chunk's window
+    static constexpr int chunk_blocks(int rows) { return (rows * RR + 15) / 16; }
+};
+
+template <int FM, int KS, int SA, int LDSB, int MINB, typename E>
+__global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<WinShape<SA>::NPH> wa) {
+    using W = WinShape<SA>;
+    constexpr int FN = 4, BN = 64, TW = W::TW;
+    // output rows of partial sums in LDS at a time
+    constexpr int RED = W::BASE + 4 * KS * FN * 1024 <= LDSB ? 4 : 2;
+    static_assert(FM % KS == 0 && KS % RED == 0, "rows");
+    static_assert(W::BASE + RED * KS * FN * 1024 <= LDSB, "partial sums");
+    __shared__ __attribute__((aligned(1024))) int8_t lds[LDSB];
+    uint2 *const s_tab = reinterpret_cast<uint2 *>(lds);   // step -> (window offset, weight offset)
+    float *const s_col = reinterpret_cast<float *>(lds + W::TAB * 8);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // block -> (tile, phase, column group), the last fastest: neighbours read
+    // the same window
+    int rest = xcd_logical_tile();
+    const int tn = wa.p[0].tiles_n, per = wa.p[0].tiles_h * wa.p[0].tiles_w;
+    Tile tile;
+    tile.n0 = rest % tn * BN;
+    rest /= tn;
+    const int ph = W::NPH == 1 ? 0 : rest % wa.nph;
+    if (W::NPH > 1) rest /= wa.nph;
+    const ConvArgs &a = wa.p[ph];
+    const WinGeom &wg = wa.g[ph];
+    tile.nb = rest / per;
+    rest -= tile.nb * per;
+    tile.gi0 = rest / wa.p[0].tiles_w * FM;
+    tile.gj0 = rest % wa.p[0].tiles_w * TW;
+
+    const int cin_p = a.cin_p, nchunks = cin_p >> 6, ntaps = a.ntaps, nks = a.nksteps, nbuf = wg.nbuf;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a.xq), (short)0, (int)((int64_t)a.n * a.h * a.w * cin_p), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a.wp), (short)0, (int)((int64_t)a.cout_pad * a.pack_stride), 0x00020000);
+
+    // chunks [c0, c1) of the window into their buffers: 1 KB blocks of 16
+    // records; records outside the window or the image read zeros
+    const int rows = wg.rows, nblk = W::chunk_blocks(rows), chunk_b = nblk * 1024;
+    auto fill = [&](int c0, int c1) {
+        const uint32_t px = a.xq_c64 ? 64u : (uint32_t)cin_p;
+        const uint32_t chunk_stride = a.xq_c64 ? (uint32_t)(a.h * a.w * 64) : 64u;
+        const uint32_t sample = (uint32_t)(tile.nb * a.h * a.w) * (uint32_t)cin_p;
+        const int ih0 = tile.gi0 * SA + wg.h0, iw0 = tile.gj0 * SA + wg.w0;
+        for (int b = wave; b < nblk; b += KS) {
+            const int f = 16 * b + (lane >> 2);
+            const int g = (lane & 3) ^ swz(f);
+            const int row = f / W::RR, rem = f - row * W::RR;
+            const int col = SA == 2 ? (rem < W::HCC ? 2 * rem : 2 * (rem - W::HCC) + 1) : rem;
+            const int ih = ih0 + row, iw = iw0 + col;
+            const bool in = (row < rows) & (col < wg.cols) & ((unsigned)ih < (unsigned)a.h) &
+                            ((unsigned)iw < (unsigned)a.w);
+            const uint32_t off = in ? sample + (uint32_t)(ih * a.w + iw) * px + 16u * g : kOobOffset;
+            for (int c = c0; c < c1; ++c)
+                dma16s(rx, lds + W::BASE + c % nbuf * chunk_b + b * 1024, off, (uint32_t)c * chunk_stride);
+        }
+    };
+    fill(0, nbuf < nchunks ? nbuf : nchunks);
+    // step s of the table: tap s mod ntaps of chunk s / ntaps; wave w takes the
+    // steps w, w + KS, ...
+    for (int s = tid; s < nks; s += 64 * KS) {
+        const int c = s / ntaps, t = s - c * ntaps;
+        const int i = t / wg.nkw, j = t - i * wg.nkw;
+        const int r = wg.r0 + i * wg.ri, q = wg.c0 + j * wg.cj;
+        const int rec = r * W::RR + (SA == 2 ? (q & 1) * W::HCC + (q >> 1) : q);
+        const int wt = wg.t0 + i * wg.ti + j * wg.tj;
+        s_tab[s] = make_uint2((uint32_t)(c % nbuf * chunk_b + rec * 64),
+                              (uint32_t)((wt * nchunks + c) * a.cout_pad) * 64u);
+    }
+    if (tid < BN) {
+        float ct, cb;
+        column_factor(a, tile_sx(a, tile.nb), tile.n0 + tid, ct, cb);
+        s_col[tid] = ct;
+        s_col[BN + tid] = cb;
+    }
+
+    v4i acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+
+    wait_vmcnt<0>();
+    __syncthreads();
+
+    // ---- main loop ----
+    const uint32_t la0 = (uint32_t)(W::BASE + (lane & 15) * 64 + (lane >> 4) * 16);
+    const uint32_t bl = (uint32_t)(tile.n0 * 64 + (lane & 15) * 64 + (lane >> 4) * 16);
+    auto fetch_b = [&](v4i (&b)[FN], int s) {
+        const uint32_t o = bl + s_tab[s].y;
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+            b[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(o + j * 1024u), 0, 0));
+    };
+    auto fetch_a = [&](v4i (&f)[FM], int s) {
+        const uint32_t p = win_addr(la0 + s_tab[s].x);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) f[i] = *reinterpret_cast<const v4i *>(lds + p + i * W::FROW);
+    };
+    // Weights two steps ahead, the window's fragments one (within the chunks that
+    // are in LDS); reads past the wave's last step repeat a step in range and are
+    // not used.
+    v4i b[3][FN], f[2][FM];
+    const int last = nks - 1;
+    int s = wave, c = 0;
+    int cend = nbuf < nchunks ? ntaps : nks;   // first step whose chunk is not in LDS yet
+    fetch_b(b[0], s < nks ? s : last);
+    fetch_b(b[1], s + KS < nks ? s + KS : last);
+    for (;;) {
+        if (s < cend) {
+            fetch_a(f[0], s);
+            bool done = false;
+            while (!done) {
+                unroll<6>([&](auto Pc) {
+                    constexpr int P = decltype(Pc)::value;
+                    if (done) return;
+                    const int s1 = s + KS, s2 = s + 2 * KS;
+                    fetch_b(b[(P + 2) % 3], s2 < nks ? s2 : last);
+                    fetch_a(f[(P + 1) % 2], s1 < cend ? s1 : s);
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+                            acc[i][j] =
+                                __builtin_amdgcn_mfma_i32_16x16x64_i8(b[P % 3][j], f[P % 2][i], acc[i][j], 0, 0, 0);
+                    s = s1;
+                    done = s >= cend;
+                    if (done) {
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) {
+                            const v4i t = b[(P + 1) % 3][j];
+                            b[1][j] = b[(P + 2) % 3][j];
+                            b[0][j] = t;
+                        }
+                    }
+                });
+            }
+        }
+        if (cend >= nks) break;
+        // the next chunk: with several buffers it was fetched a chunk ago (every
+        // wave waits for its own part) and the buffer just read is refilled
+        if (nbuf > 1) {
+            wait_vmcnt<0>();
+            __syncthreads();
+            if (c + nbuf < nchunks) fill(c + nbuf, c + nbuf + 1);
+        } else {
+            __syncthreads();
+            fill(c + 1, c + 2);
+            wait_vmcnt<0>();
+            __syncthreads();
+        }
+        ++c;
+        cend += ntaps;
+    }
+
+    // ---- the partial sums: RED rows at a time through LDS; row i is finished
+    // by wave i % KS ----
+    constexpr int OWN = FM > KS ? FM / KS : 1;
+    v4i sum[OWN][1][FN];
+#pragma unroll
+    for (int r0 = 0; r0 < FM; r0 += RED) {
+        __syncthreads();   // the window, or the previous rows, are done with
+        v4i *const part = reinterpret_cast<v4i *>(lds + W::BASE);
+#pragma unroll
+        for (int i = 0; i < RED; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) part[((i * KS + wave) * FN + j) * 64 + lane] = acc[r0 + i][j];
+        __syncthreads();
+        const int own = wave - r0 % KS;
+        if (own >= 0 && own < RED) {
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                v4i t = part[(own * KS * FN + j) * 64 + lane];
+#pragma unroll
+                for (int k = 1; k < KS; ++k) t += part[((own * KS + k) * FN + j) * 64 + lane];
+                sum[r0 / KS][0][j] = t;
+            }
+        }
+    }
+    float m = 0.0f;
+    bool want_abs = false;
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) {
+        Epilogue<TW, 1, FN, E> ep(a, tile, (wave + o * KS) * TW, lane, s_col, s_col + BN);
+        if (wave < FM) {
+            ep.block(sum[o], 0);
+            m = fmaxf(m, ep.wave_m);
+        }
+        want_abs = ep.fl.want_abs;
+    }
+    if (want_abs) {
+        // one atomic per block at most (as Epilogue::finish does per wave)
+        m = wave_max(m);
+        float *const red = s_col + 2 * BN - KS;
+        __syncthreads();
+        if (lane == 0) red[wave] = m;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int k = 1; k < KS; ++k) m = fmaxf(m, red[k]);
+            if (m > __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + tile.nb),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                atomic_max_nonneg(a.next_absmax + tile.nb, m);
+        }
+    }
+}
+
+// The launch's arguments for tiles of FM output rows, if its geometry fits: input
+// stride 1 or 2, kernel spans of at most 9 or 6, taps on a grid, 64-column blocks
+// in the epilogue (no order that spans several), a chunk's window within the LDS
+// of a block, 32-bit buffer offsets.
+template <int SA>
+bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *out) {
+    using W = WinShape<SA>;
+    if (nph < 1 || nph > W::NPH) return false;
+    out->nph = nph;
+    int th = 1, tw = 1;
+    for (int i = 0; i < nph; ++i) {
+        const ConvArgs &a = p[i];
+        const int nchunks = a.cin_p / 64;
+        if (a.cin_p % 64 || a.cout_pad % 64 || a.sa != SA || a.n_base || wide_needed(a)) return false;
+        if (a.ntaps < 1 || a.nksteps != a.ntaps * nchunks || a.nksteps > W::TAB) return false;
+        if ((int64_t)a.n * a.h * a.w * a.cin_p >= ((int64_t)1 << 31) ||
+            (int64_t)a.cout_pad * a.pack_stride >= ((int64_t)1 << 31))
+            return false;
+        // the taps as a grid: rows of nkw taps, equal steps
+        int nkw = 1;
+        while (nkw < a.ntaps && a.dh[nkw] == a.dh[0]) ++nkw;
+        const int nkh = a.ntaps / nkw;
+        const int ri = nkh > 1 ? a.dh[nkw] - a.dh[0] : 0, cj = nkw > 1 ? a.dw[1] - a.dw[0] : 0;
+        const int ti = nkh > 1 ? a.wtap[nkw] - a.wtap[0] : 0, tj = nkw > 1 ? a.wtap[1] - a.wtap[0] : 0;
+        if (nkh * nkw != a.ntaps) return false;
+        for (int t = 0; t < a.ntaps; ++t) {
+            const int y = t / nkw, x = t % nkw;
+            if (a.dh[t] != a.dh[0] + y * ri || a.dw[t] != a.dw[0] + x * cj || a.wtap[t] != a.wtap[0] + y * ti + x * tj)
+                return false;
+        }
+        const int spanh = (ri < 0 ? -ri : ri) * (nkh - 1), spanw = (cj < 0 ? -cj : cj) * (nkw - 1);
+        const int r0 = ri < 0 ? spanh : 0, c0 = cj < 0 ? spanw : 0;   // the first tap's window position
+        WinGeom &g = out->g[i];
+        g.h0 = a.bah + a.dh[0] - r0;
+        g.w0 = a.baw + a.dw[0] - c0;
+        g.rows = (FM - 1) * SA + spanh + 1;
+        g.cols = (W::TW - 1) * SA + spanw + 1;
+        g.nkw = nkw;
+        g.r0 = r0;
+        g.ri = ri;
+        g.c0 = c0;
+        g.cj = cj;
+        g.t0 = a.wtap[0];
+        g.ti = ti;
+        g.tj = tj;
+        g.nbuf = (LDSB - W::BASE) / (W::chunk_blocks(g.rows) * 1024);
+        g.nbuf = g.nbuf < nchunks ? g.nbuf : nchunks;
+        if (g.cols > W::RR || g.nbuf < 1) return false;
+        th = (a.gh + FM - 1) / FM > th ? (a.gh + FM - 1) / FM : th;
+        tw = (a.gw + W::TW - 1) / W::TW > tw ? (a.gw + W::TW - 1) / W::TW : tw;
+        out->p[i] = a;
+    }
+    for (int i = 0; i < nph; ++i) {
+        out->p[i].tiles_h = th;
+        out->p[i].tiles_w = tw;
+        out->p[i].tiles_n = p[i].cout_pad / 64;
+    }
+    return true;
+}
+template <typename A>
+int64_t win_blocks(const A &w) {
+    return (int64_t)w.p[0].n * w.p[0].tiles_h * w.p[0].tiles_w * w.p[0].tiles_n * w.nph;
+}
+
+#define HATQ_WIN_EPILOGUES \
+    Epi<0, 64>, Epi<0, 1>, Epi<0, 0>, Epi<64, 64>, Epi<64, 1>, Epi<64, 0>, Epi<0, 64, 2>, Epi<0, 1, 2>, \
+        HATQ_GENERIC_EPILOGUES
+
+template <int FM, int KS, int SA, int LDSB, int MINB>
+hipError_t launch_win(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
+    WinArgs<WinShape<SA>::NPH> w;
+    *hit = win_args<SA>(p, nph, FM, LDSB, &w);
+    if (!*hit) return hipSuccess;
+    const int64_t blocks = win_blocks(w);
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    return with_epilogue<HATQ_WIN_EPILOGUES>(p[0], [&](auto e) {
+        conv_win_kernel<FM, KS, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * KS, 0, st>>>(w);
+        return hipGetLastError();
+    });
+}
+
 // Blocks of a persistent grid: the CU count of the current device rounded
 // down to a multiple of 8 (so a virtual block keeps its XCD), or 0 if unknown.
 int persistent_blocks() {
@@ -3284,6 +3628,8 @@ hipError_t conv_part_gather1(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_gather2(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_gather3(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_gather4(const ConvArgs &a, hipStream_t st);
+hipError_t conv_part_win2(const ConvArgs &a, int fm, bool *hit, hipStream_t st);
+hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStream_t st);
 
 #if HATQ_PART(1)
 hipError_t conv_part_halo192_a(const ConvArgs &a, bool *hit, hipStream_t st, int n_base, bool split) {
@@ -3380,10 +3726,48 @@ HATQ_GATHER_PART(3)
 HATQ_GATHER_PART(4)
 #endif
 
+#if HATQ_PART(14)
+hipError_t conv_part_win2(const ConvArgs &a, int fm, bool *hit, hipStream_t st) {
+    return fm == 4 ? launch_win<4, 4, 2, 81920, 2>(&a, 1, hit, st) : launch_win<8, 4, 2, 81920, 2>(&a, 1, hit, st);
+}
+#endif
+#if HATQ_PART(15)
+hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStream_t st) {
+    return fm == 4 ? launch_win<4, 4, 1, 54272, 3>(p, nph, hit, st) : launch_win<8, 4, 1, 81920, 2>(p, nph, hit, st);
+}
+#endif
+
 #if HATQ_PART(0)
-hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st) {
-    if (clear_next && a.next_absmax && a.next_hblock > 0)
-        fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
+// Output rows per tile of the small-launch window kernel (conv_win_kernel), or 0
+// for the kernels on 8 x 32 (or 4 x 32) tiles of all columns.  b4, b8: its blocks
+// at 4 and 8 rows.  Measured (us; 8x32 kernels / 4 rows / 8 rows):
+//  * 5x5 stride 2, 192 columns (conv_halo5_kernel, one block per CU, a tile of 75
+//    steps takes 41 us whatever the launch): b4 33 43/15/22, 189 44/19/23, 414
+//    41/19/20, 768 48/37/29, 840 42/32/26, 1152 51/46/47, 2304 65/77/69.  The two
+//    launches of 320 columns: 440 68/19/20, 880 71/32/26, 1960 75/64/49.
+//  * stride 1 and transposed (conv_pipe_kernel, four phase launches for the
+//    latter): b4 192 166/15/16, 960 184/33/26, 5292 134/91/80, 12672 222/156/109,
+//    19872 258/275/209; 3x3 70 15/10/12, 1188 35/20/19, 3276 68/47/41.
+//  * 1x1, too few steps to hide a block's start and end: b4 64 24/7/9, 819
+//    19/20/18, 1590 11/19/16, 2880 16/30/23 at 192 and 320 columns; the other
+//    widths, whose general kernel has run-time epilogues only, 2040 44/32/32,
+//    4620 58/58/51.
+static int win_rows(const ConvArgs *p, int nph) {
+    const ConvArgs &a = p[0];
+    if (a.cin_p % 64 || a.cout_pad % 64 || a.sa > 2) return 0;
+    const int64_t cols = (int64_t)a.n * ((a.gw + 15) / 16) * (a.cout_pad / 64) * nph;
+    const int64_t b4 = cols * ((a.gh + 3) / 4), b8 = cols * ((a.gh + 7) / 8);
+    const bool wide = a.cout_pad == 192 || a.cout_pad == 320;
+    if (a.sa == 2) {
+        if (b4 <= 600) return 4;
+        return !wide || a.k < 4 || b8 <= (a.cout_pad == 192 ? 600 : 1000) ? 8 : 0;
+    }
+    if (b4 <= (a.ntaps > 1 ? 500 : 800)) return 4;
+    return a.ntaps > 1 || !wide ? 8 : 0;
+}
+
+// One launch of the general kernels.
+static hipError_t launch_conv_one(const ConvArgs &a, hipStream_t st) {
     if (a.cin_p <= 4) {
         if (a.cin_p < 1) return hipErrorInvalidValue;
         if (a.rowrun) return a.cin_p == 3 ? conv_part_rowrun3(a, st) : conv_part_rowrun_other(a, st);
@@ -3417,6 +3801,21 @@ hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st) {
         default: return conv_part_pipe_other(a, st);
     }
 }
+hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st) {
+    const ConvArgs &a = p[0];
+    if (a.next_absmax && a.next_hblock > 0)
+        fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
+    const int fm = win_rows(p, nph);
+    if (fm) {
+        bool hit = false;
+        const hipError_t e = a.sa == 2 ? conv_part_win2(a, fm, &hit, st) : conv_part_win1(p, nph, fm, &hit, st);
+        if (hit) return e;
+    }
+    for (int i = 0; i < nph; ++i) {
+        const hipError_t e = launch_conv_one(p[i], st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 #endif
-
 }  // namespace hatq

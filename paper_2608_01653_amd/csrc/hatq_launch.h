@@ -87,9 +87,10 @@ struct ConvArgs {
     int16_t wtap[kMaxTaps];
 };
 
-// clear_next: zero next_absmax before the launch (false to keep accumulating
-// across the phase launches of one transposed convolution).
-hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st);
+// The launches of one convolution: nph = 1, or the phases of a transposed one
+// (the same tensors; next_absmax is cleared once and collects all of them).
+constexpr int kMaxPhases = 4;
+hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st);
 
 // Weight preparation: transform, per-channel scale, codes, bias.
 struct PrepArgs {

@@ -1,0 +1,99 @@
+"""The kernel of small launches (tiles of 4 or 8 output rows x 16 columns by 64
+output channels, the contraction divided over the waves of a block): ragged tiles
+in both directions, one to five input chunks (all of the window in LDS, two or
+three buffers, or one refilled chunk by chunk), kernel sizes up to its spans, the
+phases of transposed convolutions (unequal ones without output padding), and the
+launches on both sides of the limits of its dispatch.  Sums are whole numbers, so
+every path gives the same accumulators, outputs, maxima and codes bit for bit.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev, host
+from paper_2608_01653_amd import hatq, synth
+from test_gpu_parity import _layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    hatq.load()
+    torch.cuda.init()
+
+
+GEOM = [  # (n, h, w, cin, cout, k, stride, pad, transposed, out_pad, form, hblock)
+    (1, 1, 1, 64, 64, 1, 1, 0, False, 0, "DH", 64),        # one point
+    (2, 3, 17, 128, 128, 1, 1, 0, False, 0, "WH", 64),
+    (1, 9, 33, 320, 64, 3, 1, 1, False, 0, "DH", 16),      # five chunks
+    (1, 5, 16, 64, 128, 7, 1, 3, False, 0, "DH", 64),      # span 7
+    (1, 11, 20, 64, 64, 8, 1, 2, False, 0, "WH", 16),      # even kernel, span 8
+    (1, 8, 15, 64, 192, 2, 1, 0, False, 0, "DH", 64),
+    (1, 15, 31, 192, 320, 5, 2, 2, False, 0, "WH", 64),
+    (1, 16, 34, 320, 192, 5, 2, 2, False, 0, "DH", 64),    # five chunks in three buffers
+    (2, 7, 65, 128, 64, 6, 2, 2, False, 0, "WH", 16),      # the widest stride-2 span
+    (1, 18, 33, 64, 192, 4, 2, 1, False, 0, "DH", 64),
+    (1, 6, 9, 256, 256, 3, 2, 0, False, 0, "DH", 64),
+    (1, 3, 5, 192, 192, 5, 2, 2, True, 1, "DH", 64),
+    (1, 4, 17, 128, 64, 3, 2, 1, True, 0, "WH", 64),       # phases of unequal sizes
+    (2, 5, 7, 64, 192, 4, 2, 1, True, 0, "DH", 64),
+    (1, 9, 16, 320, 64, 6, 2, 2, True, 0, "WH", 16),
+]
+IDS = [f"{c[1]}x{c[2]}-{c[3]}to{c[4]}-k{c[5]}s{c[6]}{'T' if c[8] else ''}-{c[10]}{c[11]}" for c in GEOM]
+
+
+@pytest.mark.parametrize("c", GEOM, ids=IDS)
+def test_accumulators_exact(orc, c):
+    n, h, w, cin, cout, k, s, p, tr, op, form, hb = c
+    rng, wt, b, ref, layer = _layer(orc, c, 301)
+    xq = synth.int8_codes(rng, (n, h, w, ref.cin_p))
+    acc = orc.conv_int8(xq, ref.wq, stride=s, pad=p, transposed=tr, out_pad=op)
+    got = hatq.hatq_conv_int8(layer, dev(xq), torch.ones(n, device="cuda"), hatq.HATQ_OUT_I32)
+    assert np.array_equal(host(got), acc)
+
+
+# Batches of small samples: 1, some, and many of them, so that the launches take
+# the 4-row tiles, the 8-row tiles and the large-launch kernels of each geometry.
+BATCH = [
+    (9, 31, 192, 192, 5, 2, 2, False, 0, "DH", 64),
+    (9, 31, 192, 320, 5, 2, 2, False, 0, "WH", 64),
+    (17, 20, 128, 192, 4, 2, 1, False, 0, "WH", 64),
+    (17, 20, 64, 192, 6, 2, 2, False, 0, "DH", 64),
+    (9, 17, 64, 128, 5, 2, 2, False, 0, "WH", 64),
+    (9, 17, 192, 192, 1, 1, 0, False, 0, "DH", 64),
+    (5, 18, 64, 320, 1, 1, 0, False, 0, "WH", 64),
+    (9, 17, 128, 64, 3, 1, 1, False, 0, "WH", 64),
+    (5, 9, 192, 192, 5, 2, 2, True, 1, "WH", 64),
+    (4, 9, 64, 64, 3, 2, 1, True, 0, "DH", 64),
+]
+
+
+@pytest.mark.parametrize("c", BATCH, ids=[f"{c[2]}to{c[3]}-k{c[4]}s{c[5]}{'T' if c[7] else ''}-{c[9]}" for c in BATCH])
+@pytest.mark.parametrize("next_b", [1, 64])
+def test_launch_sizes_agree(c, next_b):
+    h, w, cin, cout, k, s, p, tr, op, form, hb = c
+    rng = np.random.default_rng(302)
+    wt, b = synth.layer_params(rng, cin, cout, k, tr)
+    layer = hatq.hatq_prepare_weights(hatq.desc(cin, cout, k, s, p, hb, tr, op), form, dev(wt), dev(b))
+    n = 420
+    g = torch.Generator("cuda").manual_seed(5)
+    xq = torch.randint(-127, 128, (n, h, w, cin), dtype=torch.int8, device="cuda", generator=g)
+    sx = torch.rand(n, device="cuda", generator=g) + 0.5
+
+    def run(q, sc):
+        m = torch.full((q.shape[0],), -1.0, device="cuda")
+        y = hatq.hatq_conv_int8(layer, q, sc, hatq.HATQ_OUT_F32, next_hblock=next_b, next_absmax=m)
+        yq, sq = hatq.hatq_conv_int8_requant(layer, q, sc, next_b, next_absmax=m)
+        t, _ = hatq.hatq_int_transition_params(layer, 1.0, 4000.0, next_b)
+        return [m, y, yq, sq, hatq.hatq_conv_int8_int_transition(layer, q, next_b, t)]
+
+    big = run(xq, sx)
+    for i, cnt in ((0, 1), (7, 60), (300, 120)):
+        part = run(xq[i:i + cnt].contiguous(), sx[i:i + cnt].contiguous())
+        for a, e in zip(part, big):
+            assert torch.equal(a, e[i:i + cnt])
+    # the maxima and codes are those of the output
+    q2, s2 = hatq.hatq_fwht_quant_act(big[1], next_b, absmax=big[0])
+    q3, s3 = hatq.hatq_fwht_quant_act(big[1], next_b)
+    assert torch.equal(s2, s3) and torch.equal(big[3], s2) and torch.equal(big[2], q2)
