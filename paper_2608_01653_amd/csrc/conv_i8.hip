@@ -470,24 +470,15 @@ struct Epilogue {
     int64_t rq_bias;
     uint64_t tapmask[FM];   // affine: the taps whose weight sums the pixel adjusts
     bool rq_pair, valid[FM], border[FM];
+    uint32_t *const slot;   // LDS word that collects the block's maximum, or NULL
 
     __device__ __forceinline__ Epilogue(const ConvArgs &a_, const Tile &t_, int row0_, int lane_, const float *col_t_,
-                                        const float *col_b_)
+                                        const float *col_b_, uint32_t *slot_ = nullptr)
         : a(a_), t(t_), row0(row0_), lane(lane_), p(lane_ & 15), q(lane_ >> 4), col_t(col_t_), col_b(col_b_),
-          fl(a_) {
+          fl(a_), slot(slot_) {
         // the whole tile inside the grid (wave-uniform): no row masking needed
         full = t.gi0 + (row0 + 16 * FM - 1) / TW < a.gh && t.gj0 + TW <= a.gw;
         wave_m = 0.0f;
-        // Published running maximum of this sample (read once; a stale value only
-        // costs work).  A group whose rigorous upper bound on max |B_next y| stays
-        // below it cannot raise the maximum, so its exact transform is skipped.
-        seen = -1.0f;
-        if (fl.want_abs) {
-            if (lane == 0)
-                seen = __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + t.nb),
-                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            seen = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(seen)));
-        }
         nbk = generic ? a.next_hblock : NB;
         // WH layer whose next operand uses the same blocks, with the paired
         // cancellation allowed (identity between the layers): B y = B (B z / b)
@@ -495,6 +486,17 @@ struct Epilogue {
         // the six-stage fp32 rounding factor (< 3.6e-7); 1 + 1e-4 covers it.
         // Without it every group runs both transforms.
         z_bound = a.paired && fl.wh && (generic ? a.hblock == a.next_hblock : WB == NB);
+        // Published running maximum of this sample (read once; a stale value only
+        // costs work).  A group whose rigorous upper bound on max |B_next y| stays
+        // below it cannot raise the maximum, so its exact transform is skipped.
+        // (Not waited for where nothing would be skipped.)
+        seen = -1.0f;
+        if (fl.want_abs && (slot == nullptr || z_bound)) {
+            if (lane == 0)
+                seen = __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + t.nb),
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            seen = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(seen)));
+        }
         // With no fp32 output to store, the next operand of such a layer is z
         // itself (B_next y = B B z / b = z in exact arithmetic): its maximum and
         // its codes are taken from z, and neither butterfly runs.
@@ -1147,18 +1149,26 @@ struct Epilogue {
     __device__ __forceinline__ void finish() {
         if (fl.want_abs) {
             const float m = wave_max(wave_m);
+            // With a slot the block publishes once for all its waves (device-scope
+            // atomics on one address take some 7 ns each, one after the other).
             // The running maximum only grows, so a wave whose maximum does not exceed
             // a value already published skips its atomic.  Device-scope atomics on
             // one address serialize, and most waves of a layer end up skipping.
-            if (lane == 0 && m > seen) atomic_max_nonneg(a.next_absmax + t.nb, m);
+            if (slot != nullptr) {
+                if (lane == 0)
+                    __hip_atomic_fetch_max(slot, __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            } else if (lane == 0 && m > seen) {
+                atomic_max_nonneg(a.next_absmax + t.nb, m);
+            }
         }
     }
 };
 
 template <int TW, int FM, int FN, typename E>
 __device__ __forceinline__ void epilogue_regs(const ConvArgs &a, const v4i (&acc)[FM][FN], const Tile &t,
-                                              int row0, int lane, const float *col_t, const float *col_b) {
-    Epilogue<TW, FM, FN, E> ep(a, t, row0, lane, col_t, col_b);
+                                              int row0, int lane, const float *col_t, const float *col_b,
+                                              uint32_t *slot = nullptr) {
+    Epilogue<TW, FM, FN, E> ep(a, t, row0, lane, col_t, col_b, slot);
 #pragma unroll
     for (int k = 0; k < FN / 4; ++k) ep.block(acc, k);
     ep.finish();
@@ -2866,11 +2876,13 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
     static_assert(2 * (TH - 1) + K <= 2 * G::HR && 2 * (TW - 1) + K <= 2 * G::HCC, "window size");
     // one LDS object (window halves, weight ring, the tile's column factors):
     // a second one makes the compiler wait for every LDS DMA before each read
-    __shared__ __attribute__((aligned(1024))) int8_t lds[2 * G::HALF_BYTES + SLOTS * B_BYTES + 4 * BN * 4];
+    __shared__ __attribute__((aligned(1024))) int8_t lds[2 * G::HALF_BYTES + SLOTS * B_BYTES + 4 * BN * 4 + 16];
     int8_t *const halo = lds;
     int8_t *const bring = lds + RING_BASE;
     float *const s_col = reinterpret_cast<float *>(lds + RING_BASE + SLOTS * B_BYTES);
     float *const s_raw = s_col + 2 * BN;
+    // the maxima of a tile and of the one before it (next_absmax)
+    uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_raw + 2 * BN);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -3017,6 +3029,8 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
         unroll<SLOTS - 1>([&](auto Jc) { issue_b(Jc, 0u); });
     else
         burst(1, 0);
+    if (tid < 2) s_max[tid] = 0;
+    int par = 0, prev_nb = tile.nb;   // the tile's maximum slot; the previous tile's sample
     // the raw per-channel scale and bias, while the first DMAs are in flight
     for (int c = tid; c < BN; c += kHaloThreads) column_raw(a, tile.n0 + c, s_raw[c], s_raw[BN + c]);
     if (wwave)
@@ -3165,7 +3179,20 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
         // the same for the lane-derived addresses and masks
         int elane = lane;
         asm volatile("" : "+v"(elane));
-        epilogue_regs<TW, FM, FN, E>(ka, acc, tile, wave * TM, elane, s_col, s_col + BN);
+        // next_absmax: the waves of a tile meet in an LDS slot, published once
+        // per tile, a tile later (the barrier above is past its last update).
+        // One atomic per wave cost 15 us at 176 tiles of one sample (61 -> 52 us),
+        // 172 -> 156 at 688, 238 -> 208 at 1024 tiles of 16 samples.
+        const EpiFlags<E> fl(ka);
+        if (fl.want_abs) {
+            if (tid == 0 && v != (int)blockIdx.x) {
+                atomicMax(reinterpret_cast<unsigned int *>(ka.next_absmax + prev_nb), s_max[par ^ 1]);
+                s_max[par ^ 1] = 0;
+            }
+            prev_nb = tile.nb;
+        }
+        epilogue_regs<TW, FM, FN, E>(ka, acc, tile, wave * TM, elane, s_col, s_col + BN, s_max + par);
+        par ^= 1;
     }
     v += gridDim.x;
     if (v >= ntiles) break;
@@ -3173,6 +3200,11 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
     tile = block_tile(a, xcd_tile(v, ntiles), TH, TW, BN);
   }
     wait_vmcnt<0>();   // no DMA may still be writing LDS when the block ends
+    if (EpiFlags<E>(a).want_abs) {
+        wait_lds();
+        __builtin_amdgcn_s_barrier();
+        if (tid == 0) atomicMax(reinterpret_cast<unsigned int *>(a.next_absmax + prev_nb), s_max[par ^ 1]);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -3200,18 +3232,35 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
 // SA = 1 also takes the four phases of a stride-2 transposed convolution in one
 // launch (a block belongs to one phase).
 // ---------------------------------------------------------------------------
+
+// Division by a fixed 1 <= d < 2^31 of 0 <= n < 2^31, as floor(n m / 2^(32 + s))
+// with s = ceil(log2 d) - 1 and m = ceil(2^(32 + s) / d): m d < 2^(32 + s) + d, so
+// n m / 2^(32 + s) exceeds n / d by less than n / 2^(32 + s) <= 1 / d (as d <=
+// 2^(s + 1)) and has the same floor.  A scalar multiply and a
+// shift where the compiler's division is a chain of some twenty instructions.
+struct FastDiv {
+    uint32_t m, s, d;
+    FastDiv() = default;
+    explicit FastDiv(int v) : m(0), s(0), d((uint32_t)v) {
+        if (v == 1) return;
+        while ((2u << s) < d) ++s;
+        m = (uint32_t)((((uint64_t)1 << (32 + s)) + d - 1) / d);
+    }
+    __device__ __forceinline__ int div(int n) const { return d == 1 ? n : (int)(__umulhi((uint32_t)n, m) >> s); }
+};
 struct WinGeom {
     int32_t h0, w0;       // input row and column of the window's first record: gi0 * SA + h0, gj0 * SA + w0
     int32_t rows, cols;   // window rows and columns in use
     // tap t = i * nkw + j: window position (r0 + i * ri, c0 + j * cj), weight tap t0 + i * ti + j * tj
-    int32_t nkw, r0, ri, c0, cj, t0, ti, tj;
+    int32_t r0, ri, c0, cj, t0, ti, tj;
+    FastDiv nkw, ntaps;
     int32_t nbuf;         // chunk buffers of the window in LDS
 };
 template <int NPH>
 struct WinArgs {
     ConvArgs p[NPH];
     WinGeom g[NPH];
-    int32_t nph;
+    FastDiv nph, tiles_n, tiles_w, per;   // phases, column groups, tiles of a row and of a sample
 };
 template <int SA>
 struct WinShape {
@@ -3219,8 +3268,9 @@ struct WinShape {
     static constexpr int TW = 16, HCC = 18;                  // HCC: window columns of one parity (SA = 2)
     static constexpr int RR = SA == 2 ? 2 * HCC : 24;        // records per window row: spans up to 6 (9)
     static constexpr int ROWB = RR * 64, FROW = SA * ROWB;   // bytes per window row, per output row
+    static constexpr int SPANH = SA == 2 ? 6 : 9;            // rows a kernel spans, at most
     static constexpr int TAB = 256;                          // K-steps of a launch, at most
-    static constexpr int BASE = TAB * 8 + 512;               // LDS: step table, column factors, window
+    static constexpr int BASE = TAB * 8 + 1024;              // LDS: step table, column factors, maximum, window
     static_assert(FROW % 512 == 0 && BASE % 512 == 0, "swizzle bits");
     // 1 KB blocks of one chunk's window
     static constexpr int chunk_blocks(int rows) { return (rows * RR + 15) / 16; }
@@ -3237,25 +3287,24 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
     __shared__ __attribute__((aligned(1024))) int8_t lds[LDSB];
     uint2 *const s_tab = reinterpret_cast<uint2 *>(lds);   // step -> (window offset, weight offset)
     float *const s_col = reinterpret_cast<float *>(lds + W::TAB * 8);
+    uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_col + 2 * BN);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // block -> (tile, phase, column group), the last fastest: neighbours read
     // the same window
-    int rest = xcd_logical_tile();
-    const int tn = wa.p[0].tiles_n, per = wa.p[0].tiles_h * wa.p[0].tiles_w;
-    Tile tile;
-    tile.n0 = rest % tn * BN;
-    rest /= tn;
-    const int ph = W::NPH == 1 ? 0 : rest % wa.nph;
-    if (W::NPH > 1) rest /= wa.nph;
+    const int l0 = xcd_logical_tile();
+    const int l1 = wa.tiles_n.div(l0), l2 = W::NPH == 1 ? l1 : wa.nph.div(l1);
+    const int ph = W::NPH == 1 ? 0 : l1 - l2 * (int)wa.nph.d;
     const ConvArgs &a = wa.p[ph];
     const WinGeom &wg = wa.g[ph];
-    tile.nb = rest / per;
-    rest -= tile.nb * per;
-    tile.gi0 = rest / wa.p[0].tiles_w * FM;
-    tile.gj0 = rest % wa.p[0].tiles_w * TW;
+    Tile tile;
+    tile.n0 = (l0 - l1 * (int)wa.tiles_n.d) * BN;
+    tile.nb = wa.per.div(l2);
+    const int l3 = l2 - tile.nb * (int)wa.per.d, th = wa.tiles_w.div(l3);
+    tile.gi0 = th * FM;
+    tile.gj0 = (l3 - th * (int)wa.tiles_w.d) * TW;
 
     const int cin_p = a.cin_p, nchunks = cin_p >> 6, ntaps = a.ntaps, nks = a.nksteps, nbuf = wg.nbuf;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
@@ -3263,37 +3312,48 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int8_t *>(a.wp), (short)0, (int)((int64_t)a.cout_pad * a.pack_stride), 0x00020000);
 
-    // chunks [c0, c1) of the window into their buffers: 1 KB blocks of 16
-    // records; records outside the window or the image read zeros
+    // The window: 1 KB blocks of 16 records, block wave + KS j of a chunk by this
+    // wave's instruction j; records outside the window or the image read zeros.
+    // The offsets are formed once, all together (a chain of some 400 cycles
+    // each, one after the other).
     const int rows = wg.rows, nblk = W::chunk_blocks(rows), chunk_b = nblk * 1024;
-    auto fill = [&](int c0, int c1) {
+    constexpr int FILL = (W::chunk_blocks((FM - 1) * SA + W::SPANH) + KS - 1) / KS;
+    uint32_t w_off[FILL];
+    {
         const uint32_t px = a.xq_c64 ? 64u : (uint32_t)cin_p;
-        const uint32_t chunk_stride = a.xq_c64 ? (uint32_t)(a.h * a.w * 64) : 64u;
         const uint32_t sample = (uint32_t)(tile.nb * a.h * a.w) * (uint32_t)cin_p;
         const int ih0 = tile.gi0 * SA + wg.h0, iw0 = tile.gj0 * SA + wg.w0;
-        for (int b = wave; b < nblk; b += KS) {
-            const int f = 16 * b + (lane >> 2);
+#pragma unroll
+        for (int j = 0; j < FILL; ++j) {
+            const int f = 16 * (wave + KS * j) + (lane >> 2);
             const int g = (lane & 3) ^ swz(f);
             const int row = f / W::RR, rem = f - row * W::RR;
             const int col = SA == 2 ? (rem < W::HCC ? 2 * rem : 2 * (rem - W::HCC) + 1) : rem;
             const int ih = ih0 + row, iw = iw0 + col;
             const bool in = (row < rows) & (col < wg.cols) & ((unsigned)ih < (unsigned)a.h) &
                             ((unsigned)iw < (unsigned)a.w);
-            const uint32_t off = in ? sample + (uint32_t)(ih * a.w + iw) * px + 16u * g : kOobOffset;
-            for (int c = c0; c < c1; ++c)
-                dma16s(rx, lds + W::BASE + c % nbuf * chunk_b + b * 1024, off, (uint32_t)c * chunk_stride);
+            const uint32_t off = sample + (uint32_t)(ih * a.w + iw) * px + 16u * g;
+            w_off[j] = in ? off : kOobOffset;
         }
+    }
+    const uint32_t chunk_stride = a.xq_c64 ? (uint32_t)(a.h * a.w * 64) : 64u;
+    // chunk c into buffer q
+    auto fill = [&](int c, int q) {
+#pragma unroll
+        for (int j = 0; j < FILL; ++j)
+            if (wave + KS * j < nblk)
+                dma16s(rx, lds + W::BASE + q * chunk_b + (wave + KS * j) * 1024, w_off[j], (uint32_t)c * chunk_stride);
     };
-    fill(0, nbuf < nchunks ? nbuf : nchunks);
+    for (int c = 0; c < nbuf; ++c) fill(c, c);
     // step s of the table: tap s mod ntaps of chunk s / ntaps; wave w takes the
     // steps w, w + KS, ...
     for (int s = tid; s < nks; s += 64 * KS) {
-        const int c = s / ntaps, t = s - c * ntaps;
-        const int i = t / wg.nkw, j = t - i * wg.nkw;
+        const int c = wg.ntaps.div(s), t = s - c * ntaps;
+        const int i = wg.nkw.div(t), j = t - i * (int)wg.nkw.d;
         const int r = wg.r0 + i * wg.ri, q = wg.c0 + j * wg.cj;
         const int rec = r * W::RR + (SA == 2 ? (q & 1) * W::HCC + (q >> 1) : q);
         const int wt = wg.t0 + i * wg.ti + j * wg.tj;
-        s_tab[s] = make_uint2((uint32_t)(c % nbuf * chunk_b + rec * 64),
+        s_tab[s] = make_uint2((uint32_t)((nbuf == 1 ? 0 : nbuf == nchunks ? c : c % nbuf) * chunk_b + rec * 64),
                               (uint32_t)((wt * nchunks + c) * a.cout_pad) * 64u);
     }
     if (tid < BN) {
@@ -3302,6 +3362,7 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
         s_col[tid] = ct;
         s_col[BN + tid] = cb;
     }
+    if (tid == 0) *s_max = 0;
 
     v4i acc[FM][FN];
 #pragma unroll
@@ -3371,10 +3432,10 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
         if (nbuf > 1) {
             wait_vmcnt<0>();
             __syncthreads();
-            if (c + nbuf < nchunks) fill(c + nbuf, c + nbuf + 1);
+            if (c + nbuf < nchunks) fill(c + nbuf, c % nbuf);
         } else {
             __syncthreads();
-            fill(c + 1, c + 2);
+            fill(c + 1, 0);
             wait_vmcnt<0>();
             __syncthreads();
         }
@@ -3391,42 +3452,32 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
         __syncthreads();   // the window, or the previous rows, are done with
         v4i *const part = reinterpret_cast<v4i *>(lds + W::BASE);
 #pragma unroll
-        for (int i = 0; i < RED; ++i)
+        for (int i = 0; i < RED; ++i) {
+            if (wave == (r0 + i) % KS) {   // kept by its owner
 #pragma unroll
-            for (int j = 0; j < FN; ++j) part[((i * KS + wave) * FN + j) * 64 + lane] = acc[r0 + i][j];
+                for (int j = 0; j < FN; ++j) sum[r0 / KS][0][j] = acc[r0 + i][j];
+            } else {
+#pragma unroll
+                for (int j = 0; j < FN; ++j) part[((i * KS + wave) * FN + j) * 64 + lane] = acc[r0 + i][j];
+            }
+        }
         __syncthreads();
         const int own = wave - r0 % KS;
         if (own >= 0 && own < RED) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                v4i t = part[(own * KS * FN + j) * 64 + lane];
+            for (int k = 1; k < KS; ++k)
 #pragma unroll
-                for (int k = 1; k < KS; ++k) t += part[((own * KS + k) * FN + j) * 64 + lane];
-                sum[r0 / KS][0][j] = t;
-            }
+                for (int j = 0; j < FN; ++j)
+                    sum[r0 / KS][0][j] += part[((own * KS + (wave + k) % KS) * FN + j) * 64 + lane];
         }
     }
-    float m = 0.0f;
-    bool want_abs = false;
 #pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-        Epilogue<TW, 1, FN, E> ep(a, tile, (wave + o * KS) * TW, lane, s_col, s_col + BN);
-        if (wave < FM) {
-            ep.block(sum[o], 0);
-            m = fmaxf(m, ep.wave_m);
-        }
-        want_abs = ep.fl.want_abs;
-    }
-    if (want_abs) {
-        // one atomic per block at most (as Epilogue::finish does per wave)
-        m = wave_max(m);
-        float *const red = s_col + 2 * BN - KS;
-        __syncthreads();
-        if (lane == 0) red[wave] = m;
+    for (int o = 0; o < OWN; ++o)
+        epilogue_regs<TW, 1, FN, E>(a, sum[o], tile, (wave + o * KS) * TW, lane, s_col, s_col + BN, s_max);
+    if (EpiFlags<E>(a).want_abs) {
         __syncthreads();
         if (tid == 0) {
-#pragma unroll
-            for (int k = 1; k < KS; ++k) m = fmaxf(m, red[k]);
+            const float m = __uint_as_float(*s_max);
             if (m > __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a.next_absmax + tile.nb),
                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
                 atomic_max_nonneg(a.next_absmax + tile.nb, m);
@@ -3442,7 +3493,6 @@ template <int SA>
 bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *out) {
     using W = WinShape<SA>;
     if (nph < 1 || nph > W::NPH) return false;
-    out->nph = nph;
     int th = 1, tw = 1;
     for (int i = 0; i < nph; ++i) {
         const ConvArgs &a = p[i];
@@ -3471,7 +3521,8 @@ bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>
         g.w0 = a.baw + a.dw[0] - c0;
         g.rows = (FM - 1) * SA + spanh + 1;
         g.cols = (W::TW - 1) * SA + spanw + 1;
-        g.nkw = nkw;
+        g.nkw = FastDiv(nkw);
+        g.ntaps = FastDiv(a.ntaps);
         g.r0 = r0;
         g.ri = ri;
         g.c0 = c0;
@@ -3481,7 +3532,7 @@ bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>
         g.tj = tj;
         g.nbuf = (LDSB - W::BASE) / (W::chunk_blocks(g.rows) * 1024);
         g.nbuf = g.nbuf < nchunks ? g.nbuf : nchunks;
-        if (g.cols > W::RR || g.nbuf < 1) return false;
+        if (g.cols > W::RR || spanh + 1 > W::SPANH || g.nbuf < 1) return false;
         th = (a.gh + FM - 1) / FM > th ? (a.gh + FM - 1) / FM : th;
         tw = (a.gw + W::TW - 1) / W::TW > tw ? (a.gw + W::TW - 1) / W::TW : tw;
         out->p[i] = a;
@@ -3491,11 +3542,16 @@ bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>
         out->p[i].tiles_w = tw;
         out->p[i].tiles_n = p[i].cout_pad / 64;
     }
+    if ((int64_t)p[0].n * th * tw * (p[0].cout_pad / 64) * nph >= ((int64_t)1 << 31)) return false;
+    out->nph = FastDiv(nph);
+    out->tiles_n = FastDiv(p[0].cout_pad / 64);
+    out->tiles_w = FastDiv(tw);
+    out->per = FastDiv(th * tw);
     return true;
 }
 template <typename A>
 int64_t win_blocks(const A &w) {
-    return (int64_t)w.p[0].n * w.p[0].tiles_h * w.p[0].tiles_w * w.p[0].tiles_n * w.nph;
+    return (int64_t)w.p[0].n * w.per.d * w.tiles_n.d * w.nph.d;
 }
 
 #define HATQ_WIN_EPILOGUES \
@@ -3508,7 +3564,6 @@ hipError_t launch_win(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
     *hit = win_args<SA>(p, nph, FM, LDSB, &w);
     if (!*hit) return hipSuccess;
     const int64_t blocks = win_blocks(w);
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     return with_epilogue<HATQ_WIN_EPILOGUES>(p[0], [&](auto e) {
         conv_win_kernel<FM, KS, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * KS, 0, st>>>(w);
         return hipGetLastError();
