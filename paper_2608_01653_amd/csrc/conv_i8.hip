@@ -3485,6 +3485,151 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
     }
 }
 
+// The same tiles where there are enough of them (stride 1 and transposed, every
+// chunk of the window in LDS): a wave takes whole units of 64 columns (of one
+// phase) of the block's tile one after the other, all K-steps of a unit itself, so
+// nothing is added up between waves and the main loop has no barrier; a block
+// loads the window once for all columns and phases.  At (4, 127, 95) transposed
+// 192 -> 192 a unit has 12-27 steps: divided over four waves, the partial sums,
+// the window and the block's start cost four times the products.
+template <int SA>
+struct ColsShape {
+    static constexpr int MAXCOLS = 320;
+    static constexpr int BASE = WinShape<SA>::TAB * 8 + MAXCOLS * 8 + 512;   // step table, column factors, maximum
+    static_assert(BASE % 512 == 0, "swizzle bits");
+};
+template <int FM, int SA, int LDSB, int MINB, typename E>
+__global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs<WinShape<SA>::NPH> wa) {
+    using W = WinShape<SA>;
+    constexpr int FN = 4, BN = 64, TW = W::TW, BASE = ColsShape<SA>::BASE;
+    __shared__ __attribute__((aligned(1024))) int8_t lds[LDSB];
+    uint2 *const s_tab = reinterpret_cast<uint2 *>(lds);   // step -> (window offset, weight offset), phase after phase
+    float *const s_col = reinterpret_cast<float *>(lds + W::TAB * 8);
+    uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_col + 2 * ColsShape<SA>::MAXCOLS);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int nph = W::NPH == 1 ? 1 : (int)wa.nph.d, tn = (int)wa.tiles_n.d;
+    const ConvArgs &a0 = wa.p[0];
+    const int l0 = xcd_logical_tile();
+    Tile tile;
+    tile.nb = wa.per.div(l0);
+    const int l1 = l0 - tile.nb * (int)wa.per.d, th = wa.tiles_w.div(l1);
+    tile.gi0 = th * FM;
+    tile.gj0 = (l1 - th * (int)wa.tiles_w.d) * TW;
+
+    const int cin_p = a0.cin_p, nchunks = cin_p >> 6;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a0.xq), (short)0, (int)((int64_t)a0.n * a0.h * a0.w * cin_p), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int8_t *>(a0.wp), (short)0, (int)((int64_t)a0.cout_pad * a0.pack_stride), 0x00020000);
+    // the window (of all phases)
+    const int rows = wa.g[0].rows, cols = wa.g[0].cols, nblk = W::chunk_blocks(rows), chunk_b = nblk * 1024;
+    {
+        const uint32_t px = a0.xq_c64 ? 64u : (uint32_t)cin_p;
+        const uint32_t chunk_stride = a0.xq_c64 ? (uint32_t)(a0.h * a0.w * 64) : 64u;
+        const uint32_t sample = (uint32_t)(tile.nb * a0.h * a0.w) * (uint32_t)cin_p;
+        const int ih0 = tile.gi0 * SA + wa.g[0].h0, iw0 = tile.gj0 * SA + wa.g[0].w0;
+        for (int b = wave; b < nblk; b += nw) {
+            const int f = 16 * b + (lane >> 2);
+            const int g = (lane & 3) ^ swz(f);
+            const int row = f / W::RR, rem = f - row * W::RR;
+            const int col = SA == 2 ? (rem < W::HCC ? 2 * rem : 2 * (rem - W::HCC) + 1) : rem;
+            const int ih = ih0 + row, iw = iw0 + col;
+            const bool in = (row < rows) & (col < cols) & ((unsigned)ih < (unsigned)a0.h) &
+                            ((unsigned)iw < (unsigned)a0.w);
+            const uint32_t off = in ? sample + (uint32_t)(ih * a0.w + iw) * px + 16u * g : kOobOffset;
+            for (int c = 0; c < nchunks; ++c)
+                dma16s(rx, lds + BASE + c * chunk_b + b * 1024, off, (uint32_t)c * chunk_stride);
+        }
+    }
+    for (int ph = 0, base = 0; ph < nph; ++ph) {
+        const WinGeom &wg = wa.g[ph];
+        const int ntaps = (int)wg.ntaps.d, nks = ntaps * nchunks;
+        for (int s = tid; s < nks; s += blockDim.x) {
+            const int c = wg.ntaps.div(s), t = s - c * ntaps;
+            const int i = wg.nkw.div(t), j = t - i * (int)wg.nkw.d;
+            const int r = wg.r0 + i * wg.ri, q = wg.c0 + j * wg.cj;
+            const int rec = r * W::RR + (SA == 2 ? (q & 1) * W::HCC + (q >> 1) : q);
+            const int wt = wg.t0 + i * wg.ti + j * wg.tj;
+            s_tab[base + s] = make_uint2((uint32_t)(c * chunk_b + rec * 64),
+                                         (uint32_t)((wt * nchunks + c) * a0.cout_pad) * 64u);
+        }
+        base += nks;
+    }
+    const float sxv = tile_sx(a0, tile.nb);
+    for (int c = tid; c < tn * BN; c += blockDim.x)
+        column_factor(a0, sxv, c, s_col[c], s_col[ColsShape<SA>::MAXCOLS + c]);
+    if (tid == 0) *s_max = 0;
+    wait_vmcnt<0>();
+    __syncthreads();
+
+    const uint32_t la0 = (uint32_t)(BASE + (lane & 15) * 64 + (lane >> 4) * 16);
+    const uint32_t bl0 = (uint32_t)((lane & 15) * 64 + (lane >> 4) * 16);
+    // units (column group, phase), the phases rotated from one column group to
+    // the next so that each wave has long and short ones
+    const int units = tn * nph;
+    for (int u = wave; u < units; u += nw) {
+        const int cg = W::NPH == 1 ? u : wa.nph.div(u);
+        int ph = W::NPH == 1 ? 0 : u - cg * nph + cg;
+        if (W::NPH > 1) ph -= wa.nph.div(ph) * nph;
+        const ConvArgs &a = wa.p[ph];
+        const int nks = (int)wa.g[ph].ntaps.d * nchunks;
+        const uint2 *tab = s_tab;
+        for (int q = 0; q < ph; ++q) tab += (int)wa.g[q].ntaps.d * nchunks;
+        tile.n0 = cg * BN;
+        const uint32_t bl = bl0 + (uint32_t)(tile.n0 * 64);
+        auto fetch_b = [&](v4i (&b)[FN], int s) {
+            const uint32_t o = bl + tab[s].y;
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                b[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(o + j * 1024u), 0, 0));
+        };
+        auto fetch_a = [&](v4i (&f)[FM], int s) {
+            const uint32_t p = win_addr(la0 + tab[s].x);
+#pragma unroll
+            for (int i = 0; i < FM; ++i) f[i] = *reinterpret_cast<const v4i *>(lds + p + i * W::FROW);
+        };
+        v4i acc[FM][FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+        v4i b[3][FN], f[2][FM];
+        const int last = nks - 1;
+        int s = 0;
+        fetch_b(b[0], 0);
+        fetch_b(b[1], 1 < nks ? 1 : last);
+        fetch_a(f[0], 0);
+        bool done = false;
+        while (!done) {
+            unroll<6>([&](auto Pc) {
+                constexpr int P = decltype(Pc)::value;
+                if (done) return;
+                fetch_b(b[(P + 2) % 3], s + 2 < nks ? s + 2 : last);
+                fetch_a(f[(P + 1) % 2], s + 1 < nks ? s + 1 : last);
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(b[P % 3][j], f[P % 2][i], acc[i][j], 0, 0, 0);
+                done = ++s >= nks;
+            });
+        }
+        epilogue_regs<TW, FM, FN, E>(a, acc, tile, 0, lane, s_col + tile.n0,
+                                     s_col + ColsShape<SA>::MAXCOLS + tile.n0, s_max);
+    }
+    if (EpiFlags<E>(a0).want_abs) {
+        __syncthreads();
+        if (tid == 0) {
+            const float m = __uint_as_float(*s_max);
+            if (m > __uint_as_float(__hip_atomic_load(reinterpret_cast<unsigned int *>(a0.next_absmax + tile.nb),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)))
+                atomic_max_nonneg(a0.next_absmax + tile.nb, m);
+        }
+    }
+}
+
 // The launch's arguments for tiles of FM output rows, if its geometry fits: input
 // stride 1 or 2, kernel spans of at most 9 or 6, taps on a grid, 64-column blocks
 // in the epilogue (no order that spans several), a chunk's window within the LDS
@@ -3554,9 +3699,41 @@ int64_t win_blocks(const A &w) {
     return (int64_t)w.p[0].n * w.per.d * w.tiles_n.d * w.nph.d;
 }
 
-#define HATQ_WIN_EPILOGUES \
-    Epi<0, 64>, Epi<0, 1>, Epi<0, 0>, Epi<64, 64>, Epi<64, 1>, Epi<64, 0>, Epi<0, 64, 2>, Epi<0, 1, 2>, \
-        HATQ_GENERIC_EPILOGUES
+// The same for conv_cols_kernel: one window over all phases, every chunk of it in
+// LDS, the table of all phases, 64-column groups up to 320 columns.
+template <int SA>
+bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *w) {
+    using W = WinShape<SA>;
+    using C = ColsShape<SA>;
+    if (!win_args<SA>(p, nph, FM, LDSB, w)) return false;
+    int h0 = w->g[0].h0, w0 = w->g[0].w0, h1 = h0, w1 = w0, steps = 0;   // first and one past the last row and column
+    for (int i = 0; i < nph; ++i) {
+        const WinGeom &g = w->g[i];
+        h0 = g.h0 < h0 ? g.h0 : h0;
+        w0 = g.w0 < w0 ? g.w0 : w0;
+        h1 = g.h0 + g.rows > h1 ? g.h0 + g.rows : h1;
+        w1 = g.w0 + g.cols > w1 ? g.w0 + g.cols : w1;
+        steps += p[i].nksteps;
+    }
+    const int nchunks = p[0].cin_p / 64, rows = h1 - h0, cols = w1 - w0;
+    if (cols > W::RR || p[0].cout_pad > C::MAXCOLS || steps > W::TAB) return false;
+    if (C::BASE + nchunks * W::chunk_blocks(rows) * 1024 > LDSB) return false;
+    for (int i = 0; i < nph; ++i) {
+        WinGeom &g = w->g[i];
+        g.r0 += g.h0 - h0;
+        g.c0 += g.w0 - w0;
+        g.h0 = h0;
+        g.w0 = w0;
+        g.rows = rows;
+        g.cols = cols;
+        g.nbuf = nchunks;
+    }
+    return true;
+}
+
+#define HATQ_WIN_FIXED \
+    Epi<0, 64>, Epi<0, 1>, Epi<0, 0>, Epi<64, 64>, Epi<64, 1>, Epi<64, 0>, Epi<0, 64, 2>, Epi<0, 1, 2>
+#define HATQ_WIN_EPILOGUES HATQ_WIN_FIXED, HATQ_GENERIC_EPILOGUES
 
 template <int FM, int KS, int SA, int LDSB, int MINB>
 hipError_t launch_win(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
@@ -3659,6 +3836,20 @@ hipError_t try_epilogue(const ConvArgs &a, bool *hit, L &&launch) {
     return r;
 }
 
+template <int FM, int SA, int LDSB, int MINB>
+hipError_t launch_cols(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
+    WinArgs<WinShape<SA>::NPH> w;
+    *hit = cols_args<SA>(p, nph, FM, LDSB, &w);
+    if (!*hit) return hipSuccess;
+    const int64_t blocks = (int64_t)w.p[0].n * w.per.d, units = (int64_t)w.tiles_n.d * w.nph.d;
+    const int waves = units < 4 ? (int)units : 4;
+    // (the run-time epilogues, which spill here, stay with conv_win_kernel)
+    return try_epilogue<HATQ_WIN_FIXED>(p[0], hit, [&](auto e) {
+        conv_cols_kernel<FM, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * waves, 0, st>>>(w);
+        return hipGetLastError();
+    });
+}
+
 }  // namespace
 
 // The dispatch is spread over several compilations of this file so that the
@@ -3685,6 +3876,7 @@ hipError_t conv_part_gather3(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_gather4(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_win2(const ConvArgs &a, int fm, bool *hit, hipStream_t st);
 hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStream_t st);
+hipError_t conv_part_cols1(const ConvArgs *p, int nph, bool *hit, hipStream_t st);
 
 #if HATQ_PART(1)
 hipError_t conv_part_halo192_a(const ConvArgs &a, bool *hit, hipStream_t st, int n_base, bool split) {
@@ -3792,6 +3984,12 @@ hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStre
 }
 #endif
 
+#if HATQ_PART(16)
+hipError_t conv_part_cols1(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
+    return launch_cols<8, 1, 81920, 2>(p, nph, hit, st);
+}
+#endif
+
 #if HATQ_PART(0)
 // Output rows per tile of the small-launch window kernel (conv_win_kernel), or 0
 // for the kernels on 8 x 32 (or 4 x 32) tiles of all columns.  b4, b8: its blocks
@@ -3819,6 +4017,23 @@ static int win_rows(const ConvArgs *p, int nph) {
     }
     if (b4 <= (a.ntaps > 1 ? 500 : 800)) return 4;
     return a.ntaps > 1 || !wide ? 8 : 0;
+}
+
+// Whether conv_cols_kernel takes the launch: stride 1 and transposed, at least
+// three units of 64 columns (of a phase) for a block's four waves, and a tile for
+// every CU (five units, two rounds of waves: for most of the block slots).
+// Measured (us; 8x32 kernels / conv_win_kernel / this one): transposed 192 -> 192
+// tiles 192 124/47/52, 240 126/58/53, 336 130/74/61, 720 257/209/-, 1188
+// 360/264/187; 3x3 192 -> 192 tiles 256 36/20/20, 512 42/46/31, 1280 109/78/65;
+// 192 -> 256 tiles 256 46/25/26, 1280 201/102/78; 192 -> 320 256 36/30/39, 512
+// 66/70/48; 1x1 192 -> 192 256 14/15/11, 1280 41/49/34; 1x1 192 -> 320 256
+// 16/21/18, 512 28/34/24; one unit 135/65/105 at 1700 tiles.
+static bool cols_units(const ConvArgs *p, int nph) {
+    const ConvArgs &a = p[0];
+    if (a.cin_p % 64 || a.cout_pad % 64 || a.sa != 1) return false;
+    const int64_t units = (int64_t)(a.cout_pad / 64) * nph;
+    const int64_t tiles = (int64_t)a.n * ((a.gh + 7) / 8) * ((a.gw + 15) / 16);
+    return units >= 3 && tiles >= (units == 5 ? 400 : 250);
 }
 
 // One launch of the general kernels.
@@ -3861,6 +4076,11 @@ hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st) {
     if (a.next_absmax && a.next_hblock > 0)
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
     const int fm = win_rows(p, nph);
+    if (cols_units(p, nph)) {
+        bool hit = false;
+        const hipError_t e = conv_part_cols1(p, nph, &hit, st);
+        if (hit) return e;
+    }
     if (fm) {
         bool hit = false;
         const hipError_t e = a.sa == 2 ? conv_part_win2(a, fm, &hit, st) : conv_part_win1(p, nph, fm, &hit, st);

@@ -1,5 +1,6 @@
-"""The kernel of small launches (tiles of 4 or 8 output rows x 16 columns by 64
-output channels, the contraction divided over the waves of a block): ragged tiles
+"""The kernels of small launches (tiles of 4 or 8 output rows x 16 columns by 64
+output channels, the contraction divided over the waves of a block) and of stride-1
+and transposed ones (tiles of 8 rows, a wave per 64 channels of a phase): ragged tiles
 in both directions, one to five input chunks (all of the window in LDS, two or
 three buffers, or one refilled chunk by chunk), kernel sizes up to its spans, the
 phases of transposed convolutions (unequal ones without output padding), and the
@@ -66,6 +67,10 @@ BATCH = [
     (9, 17, 128, 64, 3, 1, 1, False, 0, "WH", 64),
     (5, 9, 192, 192, 5, 2, 2, True, 1, "WH", 64),
     (4, 9, 64, 64, 3, 2, 1, True, 0, "DH", 64),
+    (3, 5, 320, 192, 5, 2, 2, True, 1, "WH", 64),      # every chunk of five in LDS
+    (9, 17, 64, 192, 3, 1, 1, False, 0, "DH", 64),     # three units
+    (9, 17, 64, 320, 3, 1, 1, False, 0, "WH", 64),     # five units: some waves take two
+    (9, 17, 64, 256, 1, 1, 0, False, 0, "DH", 64),
 ]
 
 
