@@ -37,7 +37,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kQuadsPerBlock = kThreads / 4;
-
 template <int B>
 __device__ __forceinline__ void load_item(const float *xs, int64_t base, int64_t E, int t,
                                           float (&v)[4 * ItemShape<B>::R]) {
@@ -56,67 +55,98 @@ __device__ __forceinline__ void load_item(const float *xs, int64_t base, int64_t
     }
 }
 
+// The reductions (absmax, min/max, range): blocks of RT threads, f(item) for
+// every item of a sample the quad takes, from the sample's end, its values in
+// registers; the loads of two items are issued before the first is used (one of
+// the widest orders).  Their blocks end in one atomic per value on an address
+// that all blocks of a sample share (or its slots), some 7 ns each, one after the
+// other: at most kRedGrid blocks of 1024 threads (two per CU) instead of up to 4096
+// of 256.  Range pass of one 50 MB sample 35 -> 17 us, of 151 MB in two 42 -> 30,
+// 604 MB in eight 105 -> 106; absmax pass of 50 MB 23 -> 11 us.  Small samples keep
+// blocks of 256 threads (2 MB: range 8.1 us, 9.4 with 16 blocks of 1024).
+constexpr int kRedGrid = 512;
+// (the order 320, 80 values per lane: 512 threads, as 128 registers spill)
 template <int B>
-__global__ void __launch_bounds__(kThreads) absmax_kernel(const float *__restrict__ x, int64_t E,
-                                                          float *__restrict__ absmax) {
-    constexpr int R = ItemShape<B>::R;
-    constexpr int I = ItemShape<B>::I;
-    const int n = blockIdx.y;
-    const float *xs = x + (int64_t)n * E;
-    const int t = threadIdx.x & 3;
-    const int64_t items = (E + I - 1) / I;
-    float m = 0.0f;
-    // (unrolled so the loads of several items are in flight together: the
-    // grid is small, so each quad walks several items)
-#pragma unroll 4
-    for (int64_t it = (int64_t)blockIdx.x * kQuadsPerBlock + (threadIdx.x >> 2); it < items;
-         it += (int64_t)gridDim.x * kQuadsPerBlock) {
+constexpr int red_threads = B > 192 ? 512 : 1024;
+constexpr int64_t kRedSmallItems = 16384;
+
+template <int B, int RT, typename F>
+__device__ __forceinline__ void for_items(const float *xs, int64_t E, int t, F &&f) {
+    constexpr int I = ItemShape<B>::I, R = ItemShape<B>::R, U = B <= 128 ? 2 : 1;
+    const int64_t items = (E + I - 1) / I, step = (int64_t)gridDim.x * (RT / 4);
+    int64_t it = (int64_t)blockIdx.x * (RT / 4) + (threadIdx.x >> 2);
+    for (; it + (U - 1) * step < items; it += U * step) {
+        float v[U][4 * R];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_item<B>(xs, (items - 1 - it - u * step) * I, E, t, v[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) f(v[u]);
+    }
+    for (; it < items; it += step) {
         float v[4 * R];
-        load_item<B>(xs, it * I, E, t, v);
+        load_item<B>(xs, (items - 1 - it) * I, E, t, v);
+        f(v);
+    }
+}
+
+// Maximum over the block of each thread's N values, one atomic per value and
+// block: out[k] holds the address of value k.
+template <int RT, int N>
+__device__ __forceinline__ void block_max(const float (&m)[N], float *const (&out)[N]) {
+    __shared__ float red[N][RT / 64];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const float w = wave_max(m[k]);
+        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        float b = red[threadIdx.x][0];
+#pragma unroll
+        for (int w = 1; w < RT / 64; ++w) b = fmaxf(b, red[threadIdx.x][w]);
+        float *dst = out[0];
+#pragma unroll
+        for (int k = 1; k < N; ++k) dst = threadIdx.x == k ? out[k] : dst;
+        atomic_max_nonneg(dst, b);
+    }
+}
+
+template <int B, int RT>
+__global__ void __launch_bounds__(RT) absmax_kernel(const float *__restrict__ x, int64_t E,
+                                                    float *__restrict__ absmax) {
+    // from the end of the batch: the codes pass then reads from its beginning,
+    // where this pass's last reads are still in the 256 MB memory-side cache
+    const int n = gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
+    float m[1] = {0.0f};
+    for_items<B, RT>(x + (int64_t)n * E, E, t, [&](auto &v) {
         fwht_item<B>(v, t);
 #pragma unroll
-        for (int r = 0; r < 4 * R; ++r) m = fmaxf(m, fabsf(v[r]));
-    }
-    m = wave_max(m);
-    __shared__ float red[kThreads / 64];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float b = red[0];
-#pragma unroll
-        for (int k = 1; k < kThreads / 64; ++k) b = fmaxf(b, red[k]);
-        atomic_max_nonneg(absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots, b);
-    }
+        for (float e : v) m[0] = fmaxf(m[0], fabsf(e));
+    });
+    block_max<RT, 1>(m, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots});
 }
 
 // The same for blocks of 1 (no transform): max |x| over the sample read as
 // float4 (E % 4 == 0), four loads per thread in flight per iteration.
-__global__ void __launch_bounds__(kThreads) absmax_flat_kernel(const float *__restrict__ x, int64_t E,
-                                                               float *__restrict__ absmax) {
-    const int n = blockIdx.y;
-    const float4 *xs = reinterpret_cast<const float4 *>(x + (int64_t)n * E);
+template <int RT>
+__global__ void __launch_bounds__(RT) absmax_flat_kernel(const float *__restrict__ x, int64_t E,
+                                                         float *__restrict__ absmax) {
+    const int n = gridDim.y - 1 - blockIdx.y;   // from the end, as absmax_kernel
     const int64_t E4 = E >> 2;
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const float4 *xs = reinterpret_cast<const float4 *>(x + (int64_t)n * E) + (E4 - 1);
+    const int64_t stride = (int64_t)gridDim.x * RT;
+    int64_t i = (int64_t)blockIdx.x * RT + threadIdx.x;
     auto m4 = [](float m, const float4 &f) {
         return fmaxf(fmaxf(fmaxf(m, fabsf(f.x)), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
     };
     float m = 0.0f;
     for (; i + 3 * stride < E4; i += 4 * stride) {
-        const float4 a = xs[i], b = xs[i + stride], c = xs[i + 2 * stride], d = xs[i + 3 * stride];
+        const float4 a = xs[-i], b = xs[-i - stride], c = xs[-i - 2 * stride], d = xs[-i - 3 * stride];
         m = m4(m4(m4(m4(m, a), b), c), d);
     }
-    for (; i < E4; i += stride) m = m4(m, xs[i]);
-    m = wave_max(m);
-    __shared__ float red[kThreads / 64];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float b = red[0];
-#pragma unroll
-        for (int k = 1; k < kThreads / 64; ++k) b = fmaxf(b, red[k]);
-        atomic_max_nonneg(absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots, b);
-    }
+    for (; i < E4; i += stride) m = m4(m, xs[-i]);
+    const float mm[1] = {m};
+    block_max<RT, 1>(mm, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots});
 }
 
 // Items per quad per loop iteration (all their loads issued before first use).
@@ -223,15 +253,16 @@ __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict
     // g - 1 (g = n / 8) and finished their last ones last, so the launch takes
     // samples last-finished first and reads each from its end: its first reads
     // meet the lines most recently written, still in the 256 MB memory-side
-    // cache (layer 3's 201 M-element input: 188 -> 181 us).  Any order gives
-    // the same codes.
+    // cache (layer 3's 201 M-element input: 188 -> 181 us).  After this call's
+    // own absmax pass (slots > 1), which reads from the end of the batch, the
+    // beginning is what was read last.  Any order gives the same codes.
     const int ns = gridDim.y;
     int n = blockIdx.y;
-    if (ns % 8 == 0) {
+    const bool rev = ns % 8 == 0 && slots == 1;
+    if (rev) {
         const int g = ns / 8, j = g - 1 - n / 8, k = n % 8;
         n = k * g + j;
     }
-    const bool rev = ns % 8 == 0;
     const float *xs = x + (int64_t)n * E;
     int8_t *qs = xq + (int64_t)n * E;
     const int t = threadIdx.x & 3;
@@ -267,43 +298,22 @@ __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict
 // ---- affine quantization (Eq. affine_q, Eq. uniform_q) ----------------------
 // Signed grid [-128, 127].  amax[k] = max(max S, 0), amax[n + k] = max(-min S, 0)
 // (both non-negative, so the order-preserving atomic serves both).
-template <int B>
-__global__ void __launch_bounds__(kThreads) minmax_kernel(const float *__restrict__ x, int64_t E,
-                                                          float *__restrict__ amax) {
-    constexpr int R = ItemShape<B>::R;
-    constexpr int I = ItemShape<B>::I;
-    const int k = blockIdx.y;
-    const float *xs = x + (int64_t)k * E;
-    const int t = threadIdx.x & 3;
-    const int64_t items = (E + I - 1) / I;
-    float hi = 0.0f, lo = 0.0f;   // max(S, 0) and max(-S, 0)
-#pragma unroll 4
-    for (int64_t it = (int64_t)blockIdx.x * kQuadsPerBlock + (threadIdx.x >> 2); it < items;
-         it += (int64_t)gridDim.x * kQuadsPerBlock) {
-        float v[4 * R];
-        load_item<B>(xs, it * I, E, t, v);
+template <int B, int RT>
+__global__ void __launch_bounds__(RT) minmax_kernel(const float *__restrict__ x, int64_t E,
+                                                    float *__restrict__ amax, int slots) {
+    const int k = gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
+    float m[2] = {0.0f, 0.0f};   // max(S, 0) and max(-S, 0)
+    for_items<B, RT>(x + (int64_t)k * E, E, t, [&](auto &v) {
         const float sigma = fwht_item<B>(v, t);
 #pragma unroll
-        for (int r = 0; r < 4 * R; ++r) {
-            const float sv = sigma * v[r];
-            hi = fmaxf(hi, sv);
-            lo = fmaxf(lo, -sv);
+        for (float e : v) {
+            const float sv = sigma * e;
+            m[0] = fmaxf(m[0], sv);
+            m[1] = fmaxf(m[1], -sv);
         }
-    }
-    hi = wave_max(hi);
-    lo = wave_max(lo);
-    __shared__ float red[2][kThreads / 64];
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = hi;
-        red[1][threadIdx.x >> 6] = lo;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        float b = red[threadIdx.x][0];
-#pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) b = fmaxf(b, red[threadIdx.x][w]);
-        atomic_max_nonneg(amax + (threadIdx.x ? gridDim.y : 0) + k, b);
-    }
+    });
+    float *dst = amax + (int64_t)k * slots + blockIdx.x % slots;
+    block_max<RT, 2>(m, {dst, dst + (int64_t)gridDim.y * slots});
 }
 
 // s = fl32(fl32(hi + lo) / 255) and z = clamp(rne(fl32(lo / s)) - 128) for a
@@ -324,16 +334,20 @@ template <int B>
 __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__restrict__ x, int64_t E,
                                                                 const float *__restrict__ amax,
                                                                 int8_t *__restrict__ xq, float *__restrict__ act_scale,
-                                                                int32_t *__restrict__ act_zero) {
+                                                                int32_t *__restrict__ act_zero, int slots) {
     constexpr int I = ItemShape<B>::I;
     constexpr int R = ItemShape<B>::R;
     const int k = blockIdx.y;
     const float *xs = x + (int64_t)k * E;
     int8_t *qs = xq + (int64_t)k * E;
     const int t = threadIdx.x & 3;
-    float s;
+    float s, hi = 0.0f, lo = 0.0f;
     int z;
-    affine_params(amax[k], amax[gridDim.y + k], s, z);
+    for (int j = 0; j < slots; ++j) {
+        hi = fmaxf(hi, amax[(int64_t)k * slots + j]);
+        lo = fmaxf(lo, amax[((int64_t)gridDim.y + k) * slots + j]);
+    }
+    affine_params(hi, lo, s, z);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         act_scale[k] = s;
         act_zero[k] = z;
@@ -365,41 +379,19 @@ __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__r
 // ---- range-expansion profiling (Eq. hadamard_sensitivity) -------------------
 // One read of x gives both maxima of each sample: max |x| (into amax[k]) and
 // max |S| of the same butterfly the quantizer applies (into amax[n + k]).
-template <int B>
-__global__ void __launch_bounds__(kThreads) range_kernel(const float *__restrict__ x, int64_t E,
-                                                         float *__restrict__ amax) {
-    constexpr int R = ItemShape<B>::R;
-    constexpr int I = ItemShape<B>::I;
-    const int k = blockIdx.y;
-    const float *xs = x + (int64_t)k * E;
-    const int t = threadIdx.x & 3;
-    const int64_t items = (E + I - 1) / I;
-    float mx = 0.0f, mh = 0.0f;
-#pragma unroll 4
-    for (int64_t it = (int64_t)blockIdx.x * kQuadsPerBlock + (threadIdx.x >> 2); it < items;
-         it += (int64_t)gridDim.x * kQuadsPerBlock) {
-        float v[4 * R];
-        load_item<B>(xs, it * I, E, t, v);
+template <int B, int RT>
+__global__ void __launch_bounds__(RT) range_kernel(const float *__restrict__ x, int64_t E,
+                                                   float *__restrict__ amax) {
+    const int k = blockIdx.y, t = threadIdx.x & 3;
+    float m[2] = {0.0f, 0.0f};   // max |x| and max |S|
+    for_items<B, RT>(x + (int64_t)k * E, E, t, [&](auto &v) {
 #pragma unroll
-        for (int r = 0; r < 4 * R; ++r) mx = fmaxf(mx, fabsf(v[r]));
+        for (float e : v) m[0] = fmaxf(m[0], fabsf(e));
         fwht_item<B>(v, t);
 #pragma unroll
-        for (int r = 0; r < 4 * R; ++r) mh = fmaxf(mh, fabsf(v[r]));
-    }
-    mx = wave_max(mx);
-    mh = wave_max(mh);
-    __shared__ float red[2][kThreads / 64];
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = mx;
-        red[1][threadIdx.x >> 6] = mh;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        float b = red[threadIdx.x][0];
-#pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) b = fmaxf(b, red[threadIdx.x][w]);
-        atomic_max_nonneg(amax + (threadIdx.x ? gridDim.y : 0) + k, b);
-    }
+        for (float e : v) m[1] = fmaxf(m[1], fabsf(e));
+    });
+    block_max<RT, 2>(m, {amax + k, amax + gridDim.y + k});
 }
 
 // Channels not a multiple of the block (or a ragged sample): one thread per
@@ -508,11 +500,6 @@ __global__ void __launch_bounds__(kThreads) scalar_kernel(const float *__restric
 #ifndef HATQ_QUANT_GRID
 #define HATQ_QUANT_GRID 65536
 #endif
-// The absmax kernels end in one atomic per block on one of the sample's
-// kAbsSlots slots.
-#ifndef HATQ_ABSMAX_GRID
-#define HATQ_ABSMAX_GRID 4096
-#endif
 int grid_x(int64_t work_units, int per_block, int n, int total = HATQ_QUANT_GRID) {
     int64_t want = (work_units + per_block - 1) / per_block;
     int64_t cap = (total + n - 1) / n;
@@ -529,13 +516,18 @@ hipError_t launch_vector(const float *x, int n, int64_t E, const float *absmax_i
     const float *A = absmax_in;
     if (!A) {
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws_absmax), n * kAbsSlots, 0u);
+        const bool small = items < kRedSmallItems;
         if constexpr (B == 1) {
-            // sixteen float4 per thread
-            const dim3 grid(grid_x(E / 4, kThreads * 16, n, HATQ_ABSMAX_GRID), n);
-            absmax_flat_kernel<<<grid, kThreads, 0, st>>>(x, E, ws_absmax);
+            // (four float4 per thread at least; twice the blocks: this pass has
+            // the fewest registers)
+            if (small)
+                absmax_flat_kernel<256><<<dim3(grid_x(E / 4, 256 * 4, n, kRedGrid), n), 256, 0, st>>>(x, E, ws_absmax);
+            else
+                absmax_flat_kernel<1024><<<dim3(grid_x(E / 4, 1024 * 4, n, 2 * kRedGrid), n), 1024, 0, st>>>(x, E, ws_absmax);
+        } else if (small) {
+            absmax_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, ws_absmax);
         } else {
-            const dim3 grid(grid_x(items, kQuadsPerBlock, n, HATQ_ABSMAX_GRID), n);
-            absmax_kernel<B><<<grid, kThreads, 0, st>>>(x, E, ws_absmax);
+            absmax_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, ws_absmax);
         }
         A = ws_absmax;
     }
@@ -566,7 +558,10 @@ hipError_t launch_range_b(const float *x, int n, int64_t P, int C, float *amax, 
     if (C % B == 0 && E % 4 == 0) {
         constexpr int I = ItemShape<B>::I;
         const int64_t items = (E + I - 1) / I;
-        range_kernel<B><<<dim3(grid_x(items, kQuadsPerBlock, n, 2048), n), kThreads, 0, st>>>(x, E, amax);
+        if (items < kRedSmallItems)
+            range_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, amax);
+        else
+            range_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, amax);
     } else if constexpr (kron_q(B) == 0) {
         const int64_t units = P * ((C + B - 1) / B);
         range_pad_kernel<B><<<dim3(grid_x(units, kThreads, n, 2048), n), kThreads, 0, st>>>(x, P, C, amax);
@@ -581,10 +576,16 @@ hipError_t launch_affine_b(const float *x, int n, int64_t E, float *ws, int8_t *
                            int32_t *act_zero, hipStream_t st) {
     constexpr int I = ItemShape<B>::I;
     const int64_t items = (E + I - 1) / I;
-    fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws), 2 * n, 0u);
-    minmax_kernel<B><<<dim3(grid_x(items, kQuadsPerBlock, n, 2048), n), kThreads, 0, st>>>(x, E, ws);
+    // the workspace is a multiple of 256 bytes: what is left of 64 floats per
+    // batch spreads the atomics of a small batch
+    const int slots = n <= 32 ? 32 / n : 1;
+    fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws), 2 * n * slots, 0u);
+    if (items < kRedSmallItems)
+        minmax_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, ws, slots);
+    else
+        minmax_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, ws, slots);
     quant_affine_kernel<B><<<dim3(grid_x(items, kQuadsPerBlock, n), n), kThreads, 0, st>>>(x, E, ws, xq, act_scale,
-                                                                                          act_zero);
+                                                                                          act_zero, slots);
     return hipGetLastError();
 }
 
