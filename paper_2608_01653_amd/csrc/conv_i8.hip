@@ -442,7 +442,9 @@ __device__ __forceinline__ void quant16(const float (&u)[16], float s, float r, 
 // work is split into the per-tile setup (constructor), one call per 64-channel
 // block of the accumulators (block(acc, k), any order) and finish(), so a
 // kernel can run a block's epilogue while later blocks' MFMAs are in flight.
-template <int TW, int FM, int FN, typename E>
+// TOT: the weight sums of the tile's 16 FN columns (affine activations) are in LDS,
+// the totals and, for a tile at the image's border, each tap's.
+template <int TW, int FM, int FN, typename E, bool TOT = false>
 struct Epilogue {
     static_assert(FN % 4 == 0, "whole 64-channel blocks");
     static constexpr int WB = E::WB, NB = E::NB;
@@ -471,11 +473,13 @@ struct Epilogue {
     uint64_t tapmask[FM];   // affine: the taps whose weight sums the pixel adjusts
     bool rq_pair, valid[FM], border[FM];
     uint32_t *const slot;   // LDS word that collects the block's maximum, or NULL
+    const int32_t *const tot, *const taps;   // TOT: the sums (LDS), [column] and [tap][column]
 
     __device__ __forceinline__ Epilogue(const ConvArgs &a_, const Tile &t_, int row0_, int lane_, const float *col_t_,
-                                        const float *col_b_, uint32_t *slot_ = nullptr)
+                                        const float *col_b_, uint32_t *slot_ = nullptr,
+                                        const int32_t *tot_ = nullptr, const int32_t *taps_ = nullptr)
         : a(a_), t(t_), row0(row0_), lane(lane_), p(lane_ & 15), q(lane_ >> 4), col_t(col_t_), col_b(col_b_),
-          fl(a_), slot(slot_) {
+          fl(a_), slot(slot_), tot(tot_), taps(taps_) {
         // the whole tile inside the grid (wave-uniform): no row masking needed
         full = t.gi0 + (row0 + 16 * FM - 1) / TW < a.gh && t.gj0 + TW <= a.gw;
         wave_m = 0.0f;
@@ -568,10 +572,27 @@ struct Epilogue {
                 const int m = row0 + 16 * i + p;
                 const int ih0 = (t.gi0 + m / TW) * a.sa + a.bah, iw0 = (t.gj0 + m % TW) * a.sa + a.baw;
                 uint64_t mk = 0;
-                for (int tp = 0; tp < a.ntaps; ++tp) {
-                    const int ih = ih0 + a.dh[tp], iw = iw0 + a.dw[tp];
-                    const bool inside = ih >= 0 && ih < a.h && iw >= 0 && iw < a.w;
-                    if (inside != all_taps) mk |= (uint64_t)1 << tp;
+                if (all_taps) {
+                    // kernel row kh, column kw reads (ih0 + kh, iw0 + kw): the
+                    // outside taps are whole rows and the outside columns of
+                    // the others (only where a lane of the group has some)
+                    const int k = a.k;
+                    const bool edge = (ih0 < 0) | (ih0 + k > a.h) | (iw0 < 0) | (iw0 + k > a.w);
+                    if (__builtin_amdgcn_ballot_w64(edge & valid[i]) != 0) {
+                        const uint32_t row = (1u << k) - 1;
+                        const int wl = iw0 < 0 ? -iw0 : 0, wr = a.w - iw0;   // columns [wl, wr) are inside
+                        const uint32_t in = wr <= 0 ? 0u : (wr >= k ? row : (1u << wr) - 1) & ~((1u << wl) - 1);
+                        for (int kh = 0; kh < k; ++kh) {
+                            const bool rin = (unsigned)(ih0 + kh) < (unsigned)a.h;
+                            mk |= (uint64_t)(rin ? row & ~in : row) << (kh * k);
+                        }
+                    }
+                } else {
+                    for (int tp = 0; tp < a.ntaps; ++tp) {
+                        const int ih = ih0 + a.dh[tp], iw = iw0 + a.dw[tp];
+                        const bool inside = ih >= 0 && ih < a.h && iw >= 0 && iw < a.w;
+                        if (inside) mk |= (uint64_t)1 << tp;
+                    }
                 }
                 tapmask[i] = valid[i] ? mk : 0;
                 border[i] = __builtin_amdgcn_ballot_w64(tapmask[i] != 0) != 0;
@@ -593,7 +614,10 @@ struct Epilogue {
         if (all_taps) {
             const int32_t *full = a.tapsum + (int64_t)a.k * a.k * a.cout_pad + cl0;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) T[jj] = *reinterpret_cast<const v4i *>(full + 16 * jj);
+            for (int jj = 0; jj < 4; ++jj) {
+                if constexpr (TOT) T[jj] = *reinterpret_cast<const v4i *>(tot + 64 * k + 16 * jj + 4 * q);
+                else T[jj] = *reinterpret_cast<const v4i *>(full + 16 * jj);
+            }
         }
         if (border[i]) {
             const int sg = all_taps ? -1 : 1;
@@ -602,9 +626,15 @@ struct Epilogue {
                 const int tp = __builtin_ctzll(mk);
                 mk &= mk - 1;
                 const int wt = all_taps ? tp : a.wtap[tp];   // every tap: the table is the identity
-                const int32_t *row = a.tapsum + (int64_t)wt * a.cout_pad + cl0;
+                if constexpr (TOT) {
+                    const int32_t *row = taps + wt * (16 * FN) + 64 * k + 4 * q;
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) T[jj] += sg * *reinterpret_cast<const v4i *>(row + 16 * jj);
+                    for (int jj = 0; jj < 4; ++jj) T[jj] += sg * *reinterpret_cast<const v4i *>(row + 16 * jj);
+                } else {
+                    const int32_t *row = a.tapsum + (int64_t)wt * a.cout_pad + cl0;
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) T[jj] += sg * *reinterpret_cast<const v4i *>(row + 16 * jj);
+                }
             }
         }
 #pragma unroll
@@ -1164,11 +1194,12 @@ struct Epilogue {
     }
 };
 
-template <int TW, int FM, int FN, typename E>
+template <int TW, int FM, int FN, typename E, bool TOT = false>
 __device__ __forceinline__ void epilogue_regs(const ConvArgs &a, const v4i (&acc)[FM][FN], const Tile &t,
                                               int row0, int lane, const float *col_t, const float *col_b,
-                                              uint32_t *slot = nullptr) {
-    Epilogue<TW, FM, FN, E> ep(a, t, row0, lane, col_t, col_b, slot);
+                                              uint32_t *slot = nullptr, const int32_t *tot = nullptr,
+                                              const int32_t *taps = nullptr) {
+    Epilogue<TW, FM, FN, E, TOT> ep(a, t, row0, lane, col_t, col_b, slot, tot, taps);
 #pragma unroll
     for (int k = 0; k < FN / 4; ++k) ep.block(acc, k);
     ep.finish();
@@ -2851,6 +2882,7 @@ __device__ __forceinline__ void unroll(F &&f) {
 template <int BN, typename E>
 __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvArgs a) {
     using G = HaloGeom;
+    constexpr bool AFFINE = E::Q == 3 || E::Q == 7;
     constexpr int K = 5, NTAP = K * K, NODD = (K >> 1) * K, SLOTS = 5;
     static_assert(NTAP % SLOTS == 0, "ring slot of a step is fixed within a chunk");
     static_assert(NTAP % 2 == 1 && NODD % 2 == 0 && SLOTS == 5, "barrier schedule");
@@ -2874,15 +2906,19 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
     static_assert((G::HALF_BYTES & 0x1FF) == 0 && (RING_BASE & 0x1FF) == 0 && (B_BYTES & 0x1FF) == 0, "swizzle bits");
     static_assert(G::HALF_BYTES + 1024 < 65536 && (SLOTS - 1) * B_BYTES + (FN - 1) * 1024 < 65536, "read offsets");
     static_assert(2 * (TH - 1) + K <= 2 * G::HR && 2 * (TW - 1) + K <= 2 * G::HCC, "window size");
+    static_assert(NTAP * BN * 4 <= G::HALF_BYTES, "weight sums of the taps");
     // one LDS object (window halves, weight ring, the tile's column factors):
     // a second one makes the compiler wait for every LDS DMA before each read
-    __shared__ __attribute__((aligned(1024))) int8_t lds[2 * G::HALF_BYTES + SLOTS * B_BYTES + 4 * BN * 4 + 16];
+    __shared__ __attribute__((aligned(1024))) int8_t lds[2 * G::HALF_BYTES + SLOTS * B_BYTES + 4 * BN * 4 + 16 +
+                                                          (AFFINE ? BN * 4 : 0)];
     int8_t *const halo = lds;
     int8_t *const bring = lds + RING_BASE;
     float *const s_col = reinterpret_cast<float *>(lds + RING_BASE + SLOTS * B_BYTES);
     float *const s_raw = s_col + 2 * BN;
     // the maxima of a tile and of the one before it (next_absmax)
     uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_raw + 2 * BN);
+    // affine activations: the total weight sums of the columns
+    int32_t *const s_tot = reinterpret_cast<int32_t *>(s_max + 4);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -3032,7 +3068,10 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
     if (tid < 2) s_max[tid] = 0;
     int par = 0, prev_nb = tile.nb;   // the tile's maximum slot; the previous tile's sample
     // the raw per-channel scale and bias, while the first DMAs are in flight
-    for (int c = tid; c < BN; c += kHaloThreads) column_raw(a, tile.n0 + c, s_raw[c], s_raw[BN + c]);
+    for (int c = tid; c < BN; c += kHaloThreads) {
+        column_raw(a, tile.n0 + c, s_raw[c], s_raw[BN + c]);
+        if constexpr (AFFINE) s_tot[c] = a.tapsum[(int64_t)K * K * a.cout_pad + tile.n0 + c];
+    }
     if (wwave)
         wait_vmcnt_lds<(SLOTS - 2) * PER>();
     else
@@ -3176,6 +3215,21 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
         // the next tile's DMAs (its odd window rows, weight steps 0-3) complete
         // before this wave issues stores: they are then not counted behind them
         wait_vmcnt<0>();
+        // affine activations, a tile at the border: each tap's weight sums into the
+        // even-row half of the window, which is free until the next tile's first
+        // step (read from memory tap by tap, their latency took 20 us of a
+        // tile's 70)
+        if constexpr (AFFINE) {
+            const int ih0 = tile.gi0 * 2 + ka.bah, iw0 = tile.gj0 * 2 + ka.baw;
+            if (ih0 < 0 || iw0 < 0 || ih0 + rows_used > ka.h || iw0 + cols_used > ka.w) {
+                for (int e = tid; e < NTAP * BN / 4; e += kHaloThreads) {
+                    const int tp = e / (BN / 4), c4 = e - tp * (BN / 4);
+                    reinterpret_cast<v4i *>(halo)[e] =
+                        *reinterpret_cast<const v4i *>(ka.tapsum + (int64_t)tp * ka.cout_pad + tile.n0 + 4 * c4);
+                }
+                __syncthreads();
+            }
+        }
         // the same for the lane-derived addresses and masks
         int elane = lane;
         asm volatile("" : "+v"(elane));
@@ -3191,7 +3245,8 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
             }
             prev_nb = tile.nb;
         }
-        epilogue_regs<TW, FM, FN, E>(ka, acc, tile, wave * TM, elane, s_col, s_col + BN, s_max + par);
+        epilogue_regs<TW, FM, FN, E, AFFINE>(ka, acc, tile, wave * TM, elane, s_col, s_col + BN, s_max + par, s_tot,
+                                             reinterpret_cast<const int32_t *>(halo));
         par ^= 1;
     }
     v += gridDim.x;

@@ -102,3 +102,55 @@ def test_launch_sizes_agree(c, next_b):
     q2, s2 = hatq.hatq_fwht_quant_act(big[1], next_b, absmax=big[0])
     q3, s3 = hatq.hatq_fwht_quant_act(big[1], next_b)
     assert torch.equal(s2, s3) and torch.equal(big[3], s2) and torch.equal(big[2], q2)
+
+
+# Affine activations on the persistent window kernel (several tiles per block, most
+# at the image's border: a tap's weight sums staged per tile) and on the kernel of
+# small launches: a batch against parts of it, bit for bit, and the 64-bit sums of
+# the centered codes on the first sample.
+@pytest.mark.parametrize("form", ["DH", "WH"])
+def test_affine_launch_sizes_agree(orc, form):
+    n, h, w, cin, cout = 150, 18, 21, 64, 192
+    rng = np.random.default_rng(303)
+    wt, b = synth.layer_params(rng, cin, cout, 5)
+    ref = orc.prepare_weights(wt, b, cin=cin, cout=cout, k=5, stride=2, pad=2, form=form, hblock=64)
+    layer = hatq.hatq_prepare_weights(hatq.desc(cin, cout, 5, 2, 2, 64), form, dev(wt), dev(b))
+    tap = hatq.hatq_weight_tapsums(layer)
+    x = torch.randn((n, h, w, cin), device="cuda", generator=torch.Generator("cuda").manual_seed(9)) + 0.7
+    q, s, z = hatq.hatq_fwht_quant_act_affine(x, 64 if form == "DH" else 1)
+    for mode in (hatq.HATQ_OUT_F32, hatq.HATQ_OUT_I32):
+        big = hatq.hatq_conv_int8_affine(layer, q, s, z, tap, out_mode=mode)
+        for i, cnt in ((0, 3), (100, 50)):
+            part = hatq.hatq_conv_int8_affine(layer, q[i:i + cnt].contiguous(), s[i:i + cnt].contiguous(),
+                                              z[i:i + cnt].contiguous(), tap, out_mode=mode)
+            assert torch.equal(part, big[i:i + cnt])
+    acc = orc.conv_int8(host(q[:1]), ref.wq, stride=2, pad=2, zx=host(z[:1]))
+    assert np.array_equal(host(big[:1]), acc)
+
+
+# The reductions' block sizes: one sample on both sides of the limit, odd counts of
+# items per block, and a batch of more samples than blocks; the absmax and minimum
+# and maximum against torch's (blocks of 1: exact), the order-64 ones against the
+# activation kernel's own codes (no code beyond the scale, and one that reaches it).
+@pytest.mark.parametrize("shape", [(1, 16, 16, 4095 * 4), (1, 127, 129, 64), (1, 128, 128, 64), (1, 129, 131, 64),
+                                   (3, 61, 67, 192), (700, 5, 3, 64)])
+@pytest.mark.parametrize("b", [1, 64])
+def test_reduction_block_sizes(shape, b):
+    if shape[3] % b:
+        shape = shape[:3] + (shape[3] // 64 * 64,)
+    n = shape[0]
+    x = torch.randn(shape, device="cuda", generator=torch.Generator("cuda").manual_seed(11))
+    for i in range(n):   # the largest value at an end of the sample
+        x[i].view(-1)[0 if i % 2 else -1] = 9.0 if i % 3 else -9.0
+    amax, _ = hatq.hatq_range_expansion(x, b)
+    q, s = hatq.hatq_fwht_quant_act(x, b)
+    qa, sa, za = hatq.hatq_fwht_quant_act_affine(x, b)
+    lim = x.abs().amax(dim=(1, 2, 3))
+    assert torch.equal(amax[:n], lim)
+    assert torch.equal(s, amax[n:] / torch.full((1,), 127.0, device="cuda"))
+    assert torch.equal(q.abs().amax(dim=(1, 2, 3)), torch.full((n,), 127, dtype=torch.int8, device="cuda"))
+    if b == 1:
+        assert torch.equal(amax[n:], lim)
+        hi, lo = x.amax(dim=(1, 2, 3)).clamp_min(0), (-x).amax(dim=(1, 2, 3)).clamp_min(0)
+        assert torch.equal(sa, (hi + lo) / torch.full((1,), 255.0, device="cuda"))
+    assert bool((qa.amax(dim=(1, 2, 3)) >= 126).all()) and bool((qa.amin(dim=(1, 2, 3)) <= -127).all())
