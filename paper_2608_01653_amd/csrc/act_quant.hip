@@ -90,9 +90,10 @@ __device__ __forceinline__ void for_items(const float *xs, int64_t E, int t, F &
 }
 
 // Maximum over the block of each thread's N values, one atomic per value and
-// block: out[k] holds the address of value k.
+// block: out[k] holds the address of value k.  own: the block is the only one that
+// writes there, and the memory need not hold anything before.
 template <int RT, int N>
-__device__ __forceinline__ void block_max(const float (&m)[N], float *const (&out)[N]) {
+__device__ __forceinline__ void block_max(const float (&m)[N], float *const (&out)[N], bool own = false) {
     __shared__ float red[N][RT / 64];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -107,13 +108,22 @@ __device__ __forceinline__ void block_max(const float (&m)[N], float *const (&ou
         float *dst = out[0];
 #pragma unroll
         for (int k = 1; k < N; ++k) dst = threadIdx.x == k ? out[k] : dst;
-        atomic_max_nonneg(dst, b);
+        if (own) *dst = b;
+        else atomic_max_nonneg(dst, b);
     }
+}
+
+// Maximum of a sample's slots (at most 64, non-negative): a slot per lane; read one
+// after the other they took 3 us before a block's first load.
+__device__ __forceinline__ float slots_max(const float *p, int slots) {
+    if (slots == 1) return *p;
+    const int lane = threadIdx.x & 63;
+    return wave_max(lane < slots ? p[lane] : 0.0f);
 }
 
 template <int B, int RT>
 __global__ void __launch_bounds__(RT) absmax_kernel(const float *__restrict__ x, int64_t E,
-                                                    float *__restrict__ absmax) {
+                                                    float *__restrict__ absmax, int own) {
     // from the end of the batch: the codes pass then reads from its beginning,
     // where this pass's last reads are still in the 256 MB memory-side cache
     const int n = gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
@@ -123,14 +133,14 @@ __global__ void __launch_bounds__(RT) absmax_kernel(const float *__restrict__ x,
 #pragma unroll
         for (float e : v) m[0] = fmaxf(m[0], fabsf(e));
     });
-    block_max<RT, 1>(m, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots});
+    block_max<RT, 1>(m, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots}, own != 0);
 }
 
 // The same for blocks of 1 (no transform): max |x| over the sample read as
 // float4 (E % 4 == 0), four loads per thread in flight per iteration.
 template <int RT>
 __global__ void __launch_bounds__(RT) absmax_flat_kernel(const float *__restrict__ x, int64_t E,
-                                                         float *__restrict__ absmax) {
+                                                         float *__restrict__ absmax, int own) {
     const int n = gridDim.y - 1 - blockIdx.y;   // from the end, as absmax_kernel
     const int64_t E4 = E >> 2;
     const float4 *xs = reinterpret_cast<const float4 *>(x + (int64_t)n * E) + (E4 - 1);
@@ -146,7 +156,7 @@ __global__ void __launch_bounds__(RT) absmax_flat_kernel(const float *__restrict
     }
     for (; i < E4; i += stride) m = m4(m, xs[-i]);
     const float mm[1] = {m};
-    block_max<RT, 1>(mm, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots});
+    block_max<RT, 1>(mm, {absmax + (int64_t)n * kAbsSlots + blockIdx.x % kAbsSlots}, own != 0);
 }
 
 // Items per quad per loop iteration (all their loads issued before first use).
@@ -244,7 +254,7 @@ template <int B>
 __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict__ x, int64_t E,
                                                          const float *__restrict__ absmax,
                                                          int8_t *__restrict__ xq,
-                                                         float *__restrict__ act_scale, int cc, int slots) {
+                                                         float *__restrict__ act_scale, int cc, int slots, int stride) {
     constexpr int I = ItemShape<B>::I;
     constexpr int R = ItemShape<B>::R;
     constexpr int UN = QuantUnroll<B>::UN;
@@ -254,11 +264,11 @@ __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict
     // samples last-finished first and reads each from its end: its first reads
     // meet the lines most recently written, still in the 256 MB memory-side
     // cache (layer 3's 201 M-element input: 188 -> 181 us).  After this call's
-    // own absmax pass (slots > 1), which reads from the end of the batch, the
+    // own absmax pass (stride > 1), which reads from the end of the batch, the
     // beginning is what was read last.  Any order gives the same codes.
     const int ns = gridDim.y;
     int n = blockIdx.y;
-    const bool rev = ns % 8 == 0 && slots == 1;
+    const bool rev = ns % 8 == 0 && stride == 1;
     if (rev) {
         const int g = ns / 8, j = g - 1 - n / 8, k = n % 8;
         n = k * g + j;
@@ -267,9 +277,7 @@ __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict
     int8_t *qs = xq + (int64_t)n * E;
     const int t = threadIdx.x & 3;
     // the sample's absmax: one value (given), or the maximum of its slots
-    float am = absmax[(int64_t)n * slots];
-    for (int k = 1; k < slots; ++k) am = fmaxf(am, absmax[(int64_t)n * slots + k]);
-    const float s = act_scale_from_absmax(am);
+    const float s = act_scale_from_absmax(slots_max(absmax + (int64_t)n * stride, slots));
     if (blockIdx.x == 0 && threadIdx.x == 0) act_scale[n] = s;
     const float r = 1.0f / s;
     // The fast path needs r and every t finite and normal-range; a scale below
@@ -341,13 +349,10 @@ __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__r
     const float *xs = x + (int64_t)k * E;
     int8_t *qs = xq + (int64_t)k * E;
     const int t = threadIdx.x & 3;
-    float s, hi = 0.0f, lo = 0.0f;
+    float s;
     int z;
-    for (int j = 0; j < slots; ++j) {
-        hi = fmaxf(hi, amax[(int64_t)k * slots + j]);
-        lo = fmaxf(lo, amax[((int64_t)gridDim.y + k) * slots + j]);
-    }
-    affine_params(hi, lo, s, z);
+    affine_params(slots_max(amax + (int64_t)k * slots, slots), slots_max(amax + ((int64_t)gridDim.y + k) * slots, slots),
+                  s, z);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         act_scale[k] = s;
         act_zero[k] = z;
@@ -508,32 +513,45 @@ int grid_x(int64_t work_units, int per_block, int n, int total = HATQ_QUANT_GRID
     return (int)(want < 1 ? 1 : want);
 }
 
+// A sample of at most kOwnFloats floats goes to at most kAbsSlots blocks, each with a
+// slot of its own: the slots need no clearing, one launch less (1-2 us on the GPU
+// and as much on the host).  Two-pass time without / with: order 64, 0.6 M floats 11.0 /
+// 10.0 us, 1.2 M 11.3 / 11.8; untransformed 1.2 M 10.9 / 9.8.
+template <int B>
+constexpr int64_t kOwnFloats = (int64_t)1 << (B == 1 ? 21 : 20);
+
+template <int B, int RT>
+void launch_absmax(const float *x, int n, int64_t E, float *ws, int blocks, int own, hipStream_t st) {
+    if constexpr (B == 1) absmax_flat_kernel<RT><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws, own);
+    else absmax_kernel<B, RT><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws, own);
+}
+
 template <int B>
 hipError_t launch_vector(const float *x, int n, int64_t E, const float *absmax_in, float *ws_absmax,
                          int8_t *xq, float *act_scale, hipStream_t st, int c64 = 0) {
-    constexpr int I = ItemShape<B>::I;
+    constexpr int I = ItemShape<B>::I, RT = red_threads<B>;
     const int64_t items = (E + I - 1) / I;
     const float *A = absmax_in;
-    if (!A) {
+    int slots = 1;
+    if (!A && E <= kOwnFloats<B>) {
+        // blocks of 256 threads while a quad has at most two items
+        const bool small = items <= 2 * 64 * kAbsSlots;
+        const int64_t want = (items + (small ? 64 : RT / 4) - 1) / (small ? 64 : RT / 4);
+        slots = (int)(want < kAbsSlots ? want : kAbsSlots);
+        if (small) launch_absmax<B, 256>(x, n, E, ws_absmax, slots, 1, st);
+        else launch_absmax<B, RT>(x, n, E, ws_absmax, slots, 1, st);
+        A = ws_absmax;
+    } else if (!A) {
+        slots = kAbsSlots;
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws_absmax), n * kAbsSlots, 0u);
-        const bool small = items < kRedSmallItems;
-        if constexpr (B == 1) {
-            // (four float4 per thread at least; twice the blocks: this pass has
-            // the fewest registers)
-            if (small)
-                absmax_flat_kernel<256><<<dim3(grid_x(E / 4, 256 * 4, n, kRedGrid), n), 256, 0, st>>>(x, E, ws_absmax);
-            else
-                absmax_flat_kernel<1024><<<dim3(grid_x(E / 4, 1024 * 4, n, 2 * kRedGrid), n), 1024, 0, st>>>(x, E, ws_absmax);
-        } else if (small) {
-            absmax_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, ws_absmax);
-        } else {
-            absmax_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, ws_absmax);
-        }
+        // (the untransformed pass, with the fewest registers: twice the blocks, four
+        // float4 per thread at least)
+        const int blocks = B == 1 ? grid_x(E / 4, RT * 4, n, 2 * kRedGrid) : grid_x(items, RT / 4, n, kRedGrid);
+        launch_absmax<B, RT>(x, n, E, ws_absmax, blocks, 0, st);
         A = ws_absmax;
     }
-    const int slots = absmax_in ? 1 : kAbsSlots;
     dim3 grid(grid_x(items, kQuadsPerBlock * QuantUnroll<B>::UN, n), n);
-    quant_kernel<B><<<grid, kThreads, 0, st>>>(x, E, A, xq, act_scale, c64, slots);
+    quant_kernel<B><<<grid, kThreads, 0, st>>>(x, E, A, xq, act_scale, c64, slots, absmax_in ? 1 : kAbsSlots);
     return hipGetLastError();
 }
 

@@ -4126,9 +4126,11 @@ static hipError_t launch_conv_one(const ConvArgs &a, hipStream_t st) {
         default: return conv_part_pipe_other(a, st);
     }
 }
-hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st) {
-    const ConvArgs &a = p[0];
-    if (a.next_absmax && a.next_hblock > 0)
+hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st) {
+    const ConvArgs *const p = &a;
+    const int nph = a.nph;
+    if (nph < 1 || nph > kMaxPhases) return hipErrorInvalidValue;
+    if (clear_next && a.next_absmax && a.next_hblock > 0)
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
     const int fm = win_rows(p, nph);
     if (cols_units(p, nph)) {
