@@ -3325,20 +3325,28 @@ struct WinShape {
     static constexpr int ROWB = RR * 64, FROW = SA * ROWB;   // bytes per window row, per output row
     static constexpr int SPANH = SA == 2 ? 6 : 9;            // rows a kernel spans, at most
     static constexpr int TAB = 256;                          // K-steps of a launch, at most
-    static constexpr int BASE = TAB * 8 + 1024;              // LDS: step table, column factors, maximum, window
-    static_assert(FROW % 512 == 0 && BASE % 512 == 0, "swizzle bits");
+    static_assert(FROW % 512 == 0, "swizzle bits");
     // 1 KB blocks of one chunk's window
     static constexpr int chunk_blocks(int rows) { return (rows * RR + 15) / 16; }
 };
 
-template <int FM, int KS, int SA, int LDSB, int MINB, typename E>
+// LDS before the window: step table, column factors of bn columns, the maximum.
+template <int SA>
+constexpr int win_base(int bn) {
+    return (WinShape<SA>::TAB * 8 + bn * 8 + 16 + 511) / 512 * 512;
+}
+
+template <int FM, int FN, int KS, int SA, int LDSB, int MINB, typename E>
 __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<WinShape<SA>::NPH> wa) {
     using W = WinShape<SA>;
-    constexpr int FN = 4, BN = 64, TW = W::TW;
+    constexpr int BN = 16 * FN, TW = W::TW, BASE = win_base<SA>(BN);
+    // weight fragments in flight: two steps ahead for 64 columns, one for more
+    // (a wave has the registers of two then)
+    constexpr int NB = FN == 4 ? 3 : 2;
     // output rows of partial sums in LDS at a time
-    constexpr int RED = W::BASE + 4 * KS * FN * 1024 <= LDSB ? 4 : 2;
-    static_assert(FM % KS == 0 && KS % RED == 0, "rows");
-    static_assert(W::BASE + RED * KS * FN * 1024 <= LDSB, "partial sums");
+    constexpr int RED = BASE + 4 * KS * FN * 1024 <= LDSB && FM >= 4 ? 4 : BASE + 2 * KS * FN * 1024 <= LDSB ? 2 : 1;
+    static_assert((FM % KS == 0 || KS % FM == 0) && KS % RED == 0 && FM % RED == 0, "rows");
+    static_assert(BASE + RED * KS * FN * 1024 <= LDSB, "partial sums");
     __shared__ __attribute__((aligned(1024))) int8_t lds[LDSB];
     uint2 *const s_tab = reinterpret_cast<uint2 *>(lds);   // step -> (window offset, weight offset)
     float *const s_col = reinterpret_cast<float *>(lds + W::TAB * 8);
@@ -3397,7 +3405,7 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
 #pragma unroll
         for (int j = 0; j < FILL; ++j)
             if (wave + KS * j < nblk)
-                dma16s(rx, lds + W::BASE + q * chunk_b + (wave + KS * j) * 1024, w_off[j], (uint32_t)c * chunk_stride);
+                dma16s(rx, lds + BASE + q * chunk_b + (wave + KS * j) * 1024, w_off[j], (uint32_t)c * chunk_stride);
     };
     for (int c = 0; c < nbuf; ++c) fill(c, c);
     // step s of the table: tap s mod ntaps of chunk s / ntaps; wave w takes the
@@ -3411,12 +3419,8 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
         s_tab[s] = make_uint2((uint32_t)((nbuf == 1 ? 0 : nbuf == nchunks ? c : c % nbuf) * chunk_b + rec * 64),
                               (uint32_t)((wt * nchunks + c) * a.cout_pad) * 64u);
     }
-    if (tid < BN) {
-        float ct, cb;
-        column_factor(a, tile_sx(a, tile.nb), tile.n0 + tid, ct, cb);
-        s_col[tid] = ct;
-        s_col[BN + tid] = cb;
-    }
+    const float sxv = tile_sx(a, tile.nb);
+    for (int c = tid; c < BN; c += 64 * KS) column_factor(a, sxv, tile.n0 + c, s_col[c], s_col[BN + c]);
     if (tid == 0) *s_max = 0;
 
     v4i acc[FM][FN];
@@ -3429,7 +3433,7 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
     __syncthreads();
 
     // ---- main loop ----
-    const uint32_t la0 = (uint32_t)(W::BASE + (lane & 15) * 64 + (lane >> 4) * 16);
+    const uint32_t la0 = (uint32_t)(BASE + (lane & 15) * 64 + (lane >> 4) * 16);
     const uint32_t bl = (uint32_t)(tile.n0 * 64 + (lane & 15) * 64 + (lane >> 4) * 16);
     auto fetch_b = [&](v4i (&b)[FN], int s) {
         const uint32_t o = bl + s_tab[s].y;
@@ -3442,15 +3446,15 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
 #pragma unroll
         for (int i = 0; i < FM; ++i) f[i] = *reinterpret_cast<const v4i *>(lds + p + i * W::FROW);
     };
-    // Weights two steps ahead, the window's fragments one (within the chunks that
+    // Weights NB - 1 steps ahead, the window's fragments one (within the chunks that
     // are in LDS); reads past the wave's last step repeat a step in range and are
     // not used.
-    v4i b[3][FN], f[2][FM];
+    v4i b[NB][FN], f[2][FM];
     const int last = nks - 1;
     int s = wave, c = 0;
     int cend = nbuf < nchunks ? ntaps : nks;   // first step whose chunk is not in LDS yet
-    fetch_b(b[0], s < nks ? s : last);
-    fetch_b(b[1], s + KS < nks ? s + KS : last);
+#pragma unroll
+    for (int k = 0; k < NB - 1; ++k) fetch_b(b[k], s + k * KS < nks ? s + k * KS : last);
     for (;;) {
         if (s < cend) {
             fetch_a(f[0], s);
@@ -3459,22 +3463,22 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
                 unroll<6>([&](auto Pc) {
                     constexpr int P = decltype(Pc)::value;
                     if (done) return;
-                    const int s1 = s + KS, s2 = s + 2 * KS;
-                    fetch_b(b[(P + 2) % 3], s2 < nks ? s2 : last);
+                    const int s1 = s + KS, s2 = s + (NB - 1) * KS;
+                    fetch_b(b[(P + NB - 1) % NB], s2 < nks ? s2 : last);
                     fetch_a(f[(P + 1) % 2], s1 < cend ? s1 : s);
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
 #pragma unroll
                         for (int i = 0; i < FM; ++i)
                             acc[i][j] =
-                                __builtin_amdgcn_mfma_i32_16x16x64_i8(b[P % 3][j], f[P % 2][i], acc[i][j], 0, 0, 0);
+                                __builtin_amdgcn_mfma_i32_16x16x64_i8(b[P % NB][j], f[P % 2][i], acc[i][j], 0, 0, 0);
                     s = s1;
                     done = s >= cend;
                     if (done) {
 #pragma unroll
                         for (int j = 0; j < FN; ++j) {
-                            const v4i t = b[(P + 1) % 3][j];
-                            b[1][j] = b[(P + 2) % 3][j];
+                            const v4i t = b[(P + 1) % NB][j];
+                            if constexpr (NB == 3) b[1][j] = b[(P + 2) % NB][j];
                             b[0][j] = t;
                         }
                     }
@@ -3505,7 +3509,7 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
 #pragma unroll
     for (int r0 = 0; r0 < FM; r0 += RED) {
         __syncthreads();   // the window, or the previous rows, are done with
-        v4i *const part = reinterpret_cast<v4i *>(lds + W::BASE);
+        v4i *const part = reinterpret_cast<v4i *>(lds + BASE);
 #pragma unroll
         for (int i = 0; i < RED; ++i) {
             if (wave == (r0 + i) % KS) {   // kept by its owner
@@ -3528,7 +3532,7 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
     }
 #pragma unroll
     for (int o = 0; o < OWN; ++o)
-        epilogue_regs<TW, 1, FN, E>(a, sum[o], tile, (wave + o * KS) * TW, lane, s_col, s_col + BN, s_max);
+        if (wave < FM) epilogue_regs<TW, 1, FN, E>(a, sum[o], tile, (wave + o * KS) * TW, lane, s_col, s_col + BN, s_max);
     if (EpiFlags<E>(a).want_abs) {
         __syncthreads();
         if (tid == 0) {
@@ -3690,14 +3694,14 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
 // in the epilogue (no order that spans several), a chunk's window within the LDS
 // of a block, 32-bit buffer offsets.
 template <int SA>
-bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *out) {
+bool win_args(const ConvArgs *p, int nph, int FM, int BN, int LDSB, WinArgs<WinShape<SA>::NPH> *out) {
     using W = WinShape<SA>;
     if (nph < 1 || nph > W::NPH) return false;
     int th = 1, tw = 1;
     for (int i = 0; i < nph; ++i) {
         const ConvArgs &a = p[i];
         const int nchunks = a.cin_p / 64;
-        if (a.cin_p % 64 || a.cout_pad % 64 || a.sa != SA || a.n_base || wide_needed(a)) return false;
+        if (a.cin_p % 64 || a.cout_pad % BN || a.sa != SA || a.n_base || (BN == 64 && wide_needed(a))) return false;
         if (a.ntaps < 1 || a.nksteps != a.ntaps * nchunks || a.nksteps > W::TAB) return false;
         if ((int64_t)a.n * a.h * a.w * a.cin_p >= ((int64_t)1 << 31) ||
             (int64_t)a.cout_pad * a.pack_stride >= ((int64_t)1 << 31))
@@ -3730,7 +3734,7 @@ bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>
         g.t0 = a.wtap[0];
         g.ti = ti;
         g.tj = tj;
-        g.nbuf = (LDSB - W::BASE) / (W::chunk_blocks(g.rows) * 1024);
+        g.nbuf = (LDSB - win_base<SA>(BN)) / (W::chunk_blocks(g.rows) * 1024);
         g.nbuf = g.nbuf < nchunks ? g.nbuf : nchunks;
         if (g.cols > W::RR || spanh + 1 > W::SPANH || g.nbuf < 1) return false;
         th = (a.gh + FM - 1) / FM > th ? (a.gh + FM - 1) / FM : th;
@@ -3740,11 +3744,11 @@ bool win_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>
     for (int i = 0; i < nph; ++i) {
         out->p[i].tiles_h = th;
         out->p[i].tiles_w = tw;
-        out->p[i].tiles_n = p[i].cout_pad / 64;
+        out->p[i].tiles_n = p[i].cout_pad / BN;
     }
-    if ((int64_t)p[0].n * th * tw * (p[0].cout_pad / 64) * nph >= ((int64_t)1 << 31)) return false;
+    if ((int64_t)p[0].n * th * tw * (p[0].cout_pad / BN) * nph >= ((int64_t)1 << 31)) return false;
     out->nph = FastDiv(nph);
-    out->tiles_n = FastDiv(p[0].cout_pad / 64);
+    out->tiles_n = FastDiv(p[0].cout_pad / BN);
     out->tiles_w = FastDiv(tw);
     out->per = FastDiv(th * tw);
     return true;
@@ -3760,7 +3764,7 @@ template <int SA>
 bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *w) {
     using W = WinShape<SA>;
     using C = ColsShape<SA>;
-    if (!win_args<SA>(p, nph, FM, LDSB, w)) return false;
+    if (!win_args<SA>(p, nph, FM, 64, LDSB, w)) return false;
     int h0 = w->g[0].h0, w0 = w->g[0].w0, h1 = h0, w1 = w0, steps = 0;   // first and one past the last row and column
     for (int i = 0; i < nph; ++i) {
         const WinGeom &g = w->g[i];
@@ -3793,11 +3797,11 @@ bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA
 template <int FM, int KS, int SA, int LDSB, int MINB>
 hipError_t launch_win(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
     WinArgs<WinShape<SA>::NPH> w;
-    *hit = win_args<SA>(p, nph, FM, LDSB, &w);
+    *hit = win_args<SA>(p, nph, FM, 64, LDSB, &w);
     if (!*hit) return hipSuccess;
     const int64_t blocks = win_blocks(w);
     return with_epilogue<HATQ_WIN_EPILOGUES>(p[0], [&](auto e) {
-        conv_win_kernel<FM, KS, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * KS, 0, st>>>(w);
+        conv_win_kernel<FM, 4, KS, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * KS, 0, st>>>(w);
         return hipGetLastError();
     });
 }
@@ -3905,6 +3909,20 @@ hipError_t launch_cols(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
     });
 }
 
+// conv_win_kernel on all columns of the layer, for the epilogues that transform by an
+// order across them: one block per CU (a wave holds the tile's 192 or 320 columns).
+template <int FM, int FN, int KS, int LDSB, typename... Es>
+hipError_t launch_win_wide(const ConvArgs &a, bool *hit, hipStream_t st) {
+    WinArgs<WinShape<2>::NPH> w;
+    *hit = a.cout_pad == 16 * FN && win_args<2>(&a, 1, FM, 16 * FN, LDSB, &w);
+    if (!*hit) return hipSuccess;
+    const int64_t blocks = win_blocks(w);
+    return try_epilogue<Es...>(a, hit, [&](auto e) {
+        conv_win_kernel<FM, FN, KS, 2, LDSB, 1, decltype(e)><<<(unsigned)blocks, 64 * KS, 0, st>>>(w);
+        return hipGetLastError();
+    });
+}
+
 }  // namespace
 
 // The dispatch is spread over several compilations of this file so that the
@@ -3932,6 +3950,7 @@ hipError_t conv_part_gather4(const ConvArgs &a, hipStream_t st);
 hipError_t conv_part_win2(const ConvArgs &a, int fm, bool *hit, hipStream_t st);
 hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStream_t st);
 hipError_t conv_part_cols1(const ConvArgs *p, int nph, bool *hit, hipStream_t st);
+hipError_t conv_part_win_wide(const ConvArgs &a, bool *hit, hipStream_t st);
 
 #if HATQ_PART(1)
 hipError_t conv_part_halo192_a(const ConvArgs &a, bool *hit, hipStream_t st, int n_base, bool split) {
@@ -4045,6 +4064,13 @@ hipError_t conv_part_cols1(const ConvArgs *p, int nph, bool *hit, hipStream_t st
 }
 #endif
 
+#if HATQ_PART(17)
+hipError_t conv_part_win_wide(const ConvArgs &a, bool *hit, hipStream_t st) {
+    return a.cout_pad == 192 ? launch_win_wide<4, 12, 4, 102400, HATQ_KRON192_FIXED>(a, hit, st)
+                             : launch_win_wide<2, 20, 4, 102400, HATQ_KRON320_FIXED>(a, hit, st);
+}
+#endif
+
 #if HATQ_PART(0)
 // Output rows per tile of the small-launch window kernel (conv_win_kernel), or 0
 // for the kernels on 8 x 32 (or 4 x 32) tiles of all columns.  b4, b8: its blocks
@@ -4091,6 +4117,20 @@ static bool cols_units(const ConvArgs *p, int nph) {
     return units >= 3 && tiles >= (units == 5 ? 400 : 250);
 }
 
+// Whether conv_win_kernel on all columns takes a stride-2 launch whose epilogue
+// transforms by the order 192 or 320: one block per CU, so up to one round of 4 x 16
+// tiles (192) or two of 2 x 16 (320).  Measured (us; 8x32 or 4x32 kernels / this):
+// order 192 blocks 3 41/22, 96 47/27, 256 50/31, 384 53/52, 768 62/81; order 320
+// 48 78/34, 384 83/69, 768 96/110.
+static bool wide_rows(const ConvArgs *p, int nph) {
+    const ConvArgs &a = p[0];
+    if (nph != 1 || a.sa != 2 || a.cin_p % 64 || !wide_epilogue(a)) return false;
+    if (a.cout_pad != 192 && a.cout_pad != 320) return false;
+    const int rows = a.cout_pad == 192 ? 4 : 2;
+    const int64_t blocks = (int64_t)a.n * ((a.gh + rows - 1) / rows) * ((a.gw + 15) / 16);
+    return blocks <= (a.cout_pad == 192 ? 256 : 500);
+}
+
 // One launch of the general kernels.
 static hipError_t launch_conv_one(const ConvArgs &a, hipStream_t st) {
     if (a.cin_p <= 4) {
@@ -4132,6 +4172,11 @@ hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st) {
     if (nph < 1 || nph > kMaxPhases) return hipErrorInvalidValue;
     if (clear_next && a.next_absmax && a.next_hblock > 0)
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
+    if (wide_rows(p, nph)) {
+        bool hit = false;
+        const hipError_t e = conv_part_win_wide(a, &hit, st);
+        if (hit) return e;
+    }
     const int fm = win_rows(p, nph);
     if (cols_units(p, nph)) {
         bool hit = false;

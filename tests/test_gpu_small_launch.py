@@ -154,3 +154,30 @@ def test_reduction_block_sizes(shape, b):
         hi, lo = x.amax(dim=(1, 2, 3)).clamp_min(0), (-x).amax(dim=(1, 2, 3)).clamp_min(0)
         assert torch.equal(sa, (hi + lo) / torch.full((1,), 255.0, device="cuda"))
     assert bool((qa.amax(dim=(1, 2, 3)) >= 126).all()) and bool((qa.amin(dim=(1, 2, 3)) <= -127).all())
+
+
+# Orders that span a layer's columns (192, 320): many small samples (the large-launch
+# kernels) against few of them (the kernel of small launches on all columns).
+@pytest.mark.parametrize("cout,form,hb,nb", [(192, "DH", 64, 192), (192, "WH", 192, 192), (192, "WH", 192, 1),
+                                             (320, "WH", 320, 1), (320, "DH", 64, 320)])
+def test_wide_order_launch_sizes_agree(cout, form, hb, nb):
+    rng = np.random.default_rng(304)
+    wt, b = synth.layer_params(rng, 128, cout, 5)
+    layer = hatq.hatq_prepare_weights(hatq.desc(128, cout, 5, 2, 2, hb), form, dev(wt), dev(b))
+    n = 260
+    g = torch.Generator("cuda").manual_seed(6)
+    xq = torch.randint(-127, 128, (n, 11, 35, 128), dtype=torch.int8, device="cuda", generator=g)
+    sx = torch.rand(n, device="cuda", generator=g) + 0.5
+
+    def run(q, sc):
+        m = torch.full((q.shape[0],), -1.0, device="cuda")
+        y = hatq.hatq_conv_int8(layer, q, sc, hatq.HATQ_OUT_F32, next_hblock=nb, next_absmax=m)
+        m2 = torch.full((q.shape[0],), -1.0, device="cuda")
+        hatq.hatq_conv_int8(layer, q, sc, hatq.HATQ_OUT_F32, next_hblock=nb, next_absmax=m2, absmax_only=True)
+        yq, sq = hatq.hatq_conv_int8_requant(layer, q, sc, nb, next_absmax=m)
+        return [m, y, m2, yq, sq]
+
+    big = run(xq, sx)
+    for i, cnt in ((0, 1), (37, 20), (200, 60)):
+        for a, e in zip(run(xq[i:i + cnt].contiguous(), sx[i:i + cnt].contiguous()), big):
+            assert torch.equal(a, e[i:i + cnt])
