@@ -11,7 +11,8 @@
 // register index.  Loads are 64 contiguous bytes per quad per instruction.
 //
 // Two kernels:
-//   absmax_kernel: transform, max |S| per sample (one atomic per block).
+//   absmax_kernel: transform, max |S| per sample (one value per block, into the
+//   sample's slots).
 //   quant_kernel : transform again, quantize with s = fl32(A / 127), store codes.
 // When the producer of x already computed A (next_absmax of the convolution),
 // only quant_kernel runs and x is read once.

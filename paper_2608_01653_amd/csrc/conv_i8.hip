@@ -3286,6 +3286,15 @@ __global__ void __launch_bounds__(kHaloThreads, 1) conv_halo5_kernel(const ConvA
 //
 // SA = 1 also takes the four phases of a stride-2 transposed convolution in one
 // launch (a block belongs to one phase).
+//
+// What bounds it: at 8 rows and two blocks per CU the products (a pair of blocks
+// spends 19 of its 38.5 thousand cycles at the MFMA rate; the rest is each block's
+// window, partial sums and epilogue, behind which the other block's products run
+// only in part); at 4 rows the weight loads, which in fragment order (16 rows of 16
+// bytes per quarter wave) reach 35 bytes per cycle and CU, half of a linear read's
+// rate (reordered in registers through the LDS crossbar they were no faster).  5x5
+// stride 2, 192 -> 192, (1, 256, 256): 48 -> 27 us; (1, 128, 192): 44 -> 21; 192 -> 320
+// (1, 64, 96): 68 -> 12; transposed (1, 64, 96): 105 -> 18; 1x1 (1, 64, 64, 128): 20 -> 6.
 // ---------------------------------------------------------------------------
 
 // Division by a fixed 1 <= d < 2^31 of 0 <= n < 2^31, as floor(n m / 2^(32 + s))
@@ -3317,6 +3326,7 @@ struct WinArgs {
     WinGeom g[NPH];
     FastDiv nph, tiles_n, tiles_w, per;   // phases, column groups, tiles of a row and of a sample
 };
+static_assert(sizeof(WinArgs<kMaxPhases>) <= 4096, "kernel arguments");
 template <int SA>
 struct WinShape {
     static constexpr int NPH = SA == 2 ? 1 : kMaxPhases;
