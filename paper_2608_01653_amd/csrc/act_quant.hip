@@ -592,12 +592,13 @@ hipError_t launch_range_b(const float *x, int n, int64_t P, int C, float *amax, 
 
 template <int B>
 hipError_t launch_affine_b(const float *x, int n, int64_t E, float *ws, int8_t *xq, float *act_scale,
-                           int32_t *act_zero, hipStream_t st) {
+                           int32_t *act_zero, bool spread, hipStream_t st) {
     constexpr int I = ItemShape<B>::I;
     const int64_t items = (E + I - 1) / I;
-    // the workspace is a multiple of 256 bytes: what is left of 64 floats per
-    // batch spreads the atomics of a small batch
-    const int slots = n <= 32 ? 32 / n : 1;
+    // the documented workspace is a multiple of 256 bytes: what is left of 64
+    // floats per batch spreads the atomics of a small batch (a caller may bring 2n
+    // floats only)
+    const int slots = spread && n <= 32 ? 32 / n : 1;
     fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws), 2 * n * slots, 0u);
     if (items < kRedSmallItems)
         minmax_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, ws, slots);
@@ -613,17 +614,18 @@ hipError_t launch_affine_b(const float *x, int n, int64_t E, float *ws, int8_t *
 hipError_t launch_act_quant_affine(const float *x, int n, int64_t E, int hblock, float *ws, int8_t *xq,
                                    float *act_scale, int32_t *act_zero, hipStream_t st) {
     if (E % 4 != 0) return hipErrorInvalidValue;
-    switch (hblock) {
-        case 1: return launch_affine_b<1>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 2: return launch_affine_b<2>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 4: return launch_affine_b<4>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 8: return launch_affine_b<8>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 16: return launch_affine_b<16>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 32: return launch_affine_b<32>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 64: return launch_affine_b<64>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 128: return launch_affine_b<128>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 192: return launch_affine_b<192>(x, n, E, ws, xq, act_scale, act_zero, st);
-        case 320: return launch_affine_b<320>(x, n, E, ws, xq, act_scale, act_zero, st);
+    const bool spread = (hblock & kAffineSpread) != 0;
+    switch (hblock & ~kAffineSpread) {
+        case 1: return launch_affine_b<1>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 2: return launch_affine_b<2>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 4: return launch_affine_b<4>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 8: return launch_affine_b<8>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 16: return launch_affine_b<16>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 32: return launch_affine_b<32>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 64: return launch_affine_b<64>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 128: return launch_affine_b<128>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 192: return launch_affine_b<192>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+        case 320: return launch_affine_b<320>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -145,3 +145,16 @@ def test_non_finite_input_contract(bad, b):
     y_ok = hatq.hatq_layer_forward(layer, "DH", dev(x_np))
     torch.cuda.synchronize()
     assert torch.equal(y_bad[0], y_ok[0]) and torch.equal(y_bad[2], y_ok[2])
+
+
+@pytest.mark.parametrize("n", [1, 3, 31, 33])
+def test_affine_workspace_smallest(n):
+    """8 bytes per sample are accepted: no byte past them is written, and the results
+    are those of the documented workspace."""
+    rng = np.random.default_rng(3300 + n)
+    x = dev(synth.heavy_tailed_activations(rng, (n, 5, 7, 64)))
+    ws = Guarded((8 * n,), torch.int8)
+    got = hatq.hatq_fwht_quant_act_affine(x, 64, ws=ws.view)
+    ws.check("workspace")
+    ref = hatq.hatq_fwht_quant_act_affine(x, 64)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
