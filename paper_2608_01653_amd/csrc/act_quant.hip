@@ -684,8 +684,8 @@ hipError_t launch_act_quant_noalloc(const float *x, int n, int64_t E, int hblock
     float *ws = nullptr;
     const hipError_t e = scratch_absmax(&ws);
     if (e != hipSuccess) return e;
-    // the two-pass path clears the n * kAbsSlots slots with a fill kernel
-    // before its atomics
+    // the two-pass path writes the slots that it reads (small samples) or clears
+    // all n * kAbsSlots with a fill kernel before its atomics
     return launch_act_quant(x, n, E, hblock, nullptr, ws, xq, act_scale, st);
 }
 
