@@ -580,7 +580,9 @@ struct Epilogue {
                     const bool edge = (ih0 < 0) | (ih0 + k > a.h) | (iw0 < 0) | (iw0 + k > a.w);
                     if (__builtin_amdgcn_ballot_w64(edge & valid[i]) != 0) {
                         const uint32_t row = (1u << k) - 1;
-                        const int wl = iw0 < 0 ? -iw0 : 0, wr = a.w - iw0;   // columns [wl, wr) are inside
+                        // columns [wl, wr) are inside; wl at most k, as the shift below takes
+                        // counts under 32 and the padding reaches 64
+                        const int wl = iw0 >= 0 ? 0 : -iw0 < k ? -iw0 : k, wr = a.w - iw0;
                         const uint32_t in = wr <= 0 ? 0u : (wr >= k ? row : (1u << wr) - 1) & ~((1u << wl) - 1);
                         for (int kh = 0; kh < k; ++kh) {
                             const bool rin = (unsigned)(ih0 + kh) < (unsigned)a.h;

@@ -126,3 +126,34 @@ def test_affine_layer_f32(orc, ci):
     tapsum = hatq.hatq_weight_tapsums(layer)
     y = hatq.hatq_conv_int8_affine(layer, dev(xq), dev(sx), dev(zx), tapsum, hatq.HATQ_OUT_F32)
     assert_range_rel(host(y), y_ref, what="affine layer y")
+
+
+# Padding beyond the kernel: whole kernel rows and columns outside the image, with the
+# other direction inside (the masks of the outside taps).  Small launches, stride 1
+# and 2; the persistent window kernel (12 samples: more blocks than the small-launch
+# kernel takes); the few-channel and the 1x1 kernels; 64 taps (k = 8).
+PADS = [  # (n, h, w, cin, cout, k, stride)
+    (2, 20, 18, 64, 192, 5, 2),
+    (12, 20, 18, 64, 192, 5, 2),
+    (2, 14, 21, 64, 64, 3, 1),
+    (1, 11, 9, 64, 64, 8, 1),
+    (2, 16, 37, 64, 256, 4, 2),
+    (2, 19, 22, 3, 192, 5, 2),
+    (2, 13, 12, 4, 64, 5, 2),
+    (1, 9, 7, 64, 128, 1, 1),
+]
+
+
+@pytest.mark.parametrize("pad", [2, 7, 31, 33, 64])
+@pytest.mark.parametrize("c", PADS, ids=[f"n{c[0]}-{c[1]}x{c[2]}-{c[3]}to{c[4]}-k{c[5]}s{c[6]}" for c in PADS])
+def test_affine_conv_wide_padding(orc, c, pad):
+    n, h, w, cin, cout, k, s = c
+    rng, wt, b, ref, layer = _layer(orc, (n, h, w, cin, cout, k, s, pad, False, 0, "WH", 64), 213)
+    xq = synth.int8_codes(rng, (n, h, w, ref.cin_p))
+    zx = rng.integers(-128, 128, n).astype(np.int32)
+    zx[0] = 127
+    tapsum = hatq.hatq_weight_tapsums(layer)
+    acc_ref = orc.conv_int8(xq, ref.wq, stride=s, pad=pad, zx=zx)
+    acc = hatq.hatq_conv_int8_affine(layer, dev(xq), torch.ones(n, device="cuda"), dev(zx), tapsum,
+                                     hatq.HATQ_OUT_I32)
+    assert np.array_equal(host(acc), acc_ref)
