@@ -366,7 +366,11 @@ struct EpiFlags {
     // the Kronecker variants with fixed orders take the output mode at run time
     static constexpr bool flex = generic || E::Q == 5;
     bool f32, wh, want_abs, i8, iq, affine, store;
-    __device__ explicit EpiFlags(const ConvArgs &a) {
+    // (inlined always: as a call it takes the address of the kernel's arguments, which
+    // the compiler then copies to scratch memory and reads there.  Called twice more per
+    // kernel, it was left a call in the persistent window kernel's run-time variants:
+    // 5x5 stride 2, 192 -> 192, (2, 256, 256), codes 70 -> 53 us without)
+    __device__ __forceinline__ explicit EpiFlags(const ConvArgs &a) {
         affine = E::Q == 3 || E::Q == 7;
         iq = E::Q == 2 || E::Q == 6;   // integer transition (its own variants, generic ones included)
         f32 = !iq && (generic ? a.mode != 0 : true);   // the fp32 arithmetic (F32 and I8 modes)
