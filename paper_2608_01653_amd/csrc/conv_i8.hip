@@ -470,7 +470,7 @@ struct Epilogue {
     const int row0, lane, p, q;
     const float *col_t, *col_b;
     const EpiFlags<E> fl;
-    bool full, z_bound, zpair, q_fast, kron;
+    bool z_bound, zpair, q_fast, kron;
     float wave_m, seen, qs, qr;
     int nbk, rq_n, rq_pre, zp;
     int64_t rq_bias;
@@ -484,8 +484,6 @@ struct Epilogue {
                                         const int32_t *tot_ = nullptr, const int32_t *taps_ = nullptr)
         : a(a_), t(t_), row0(row0_), lane(lane_), p(lane_ & 15), q(lane_ >> 4), col_t(col_t_), col_b(col_b_),
           fl(a_), slot(slot_), tot(tot_), taps(taps_) {
-        // the whole tile inside the grid (wave-uniform): no row masking needed
-        full = t.gi0 + (row0 + 16 * FM - 1) / TW < a.gh && t.gj0 + TW <= a.gw;
         wave_m = 0.0f;
         nbk = generic ? a.next_hblock : NB;
         // WH layer whose next operand uses the same blocks, with the paired
@@ -737,6 +735,29 @@ struct Epilogue {
         }
     }
 
+    // What is not part of the next operand.  Pixels past the grid: the transforms
+    // meet the lanes of one pixel only and codes are stored where valid, so it is
+    // enough that such a lane's maximum does not count.  Channels past cout (the
+    // padding of a WH layer's last block), which do mix: zeroed before the
+    // transform; v[4 jj + r] is channel c0 + 16 jj + 4 q + r.
+    __device__ __forceinline__ void group_max(float mm, int i) {
+        wave_m = fmaxf(wave_m, valid[i] ? mm : 0.0f);
+    }
+    template <int N>
+    __device__ __forceinline__ void drop_channels(float (&v)[N], int c0) const {
+        if (c0 + 4 * N <= a.cout) return;   // wave-uniform
+        const int left = a.cout - c0 - 4 * q;
+#pragma unroll
+        for (int e = 0; e < N; ++e) v[e] = 16 * (e / 4) + e % 4 < left ? v[e] : 0.0f;
+    }
+    template <int N>
+    static __device__ __forceinline__ float abs_max(const float (&v)[N]) {
+        float mm = 0.0f;
+#pragma unroll
+        for (int e = 0; e < N; ++e) mm = fmaxf(mm, fabsf(v[e]));
+        return mm;
+    }
+
     // The sixteen values of 64-channel block k among a row group's KV.
     template <typename T>
     static __device__ __forceinline__ T (&grp(T (&v)[KV], int k))[16] {
@@ -815,13 +836,8 @@ struct Epilogue {
                 for (int k = 0; k < NBLK; ++k) store_group(a, t, row0, lane, i, k, grp(v, k));
             }
             if (!(want_abs || i8)) continue;
-            // rows past the grid are not part of the next operand (cout is a
-            // multiple of the next block, so every channel is)
-            if (!valid[i]) {
-#pragma unroll
-                for (int r = 0; r < KV; ++r) v[r] = 0.0f;
-            }
-            // channel order matters for the codes only
+            // (cout is a multiple of the next block: every channel is part of the
+            // next operand.)  Channel order matters for the codes only.
             auto next_kron = [&]() {
                 if (i8) {
 #pragma unroll
@@ -863,10 +879,7 @@ struct Epilogue {
                     store_codes(w, i, k);
                 }
             } else {
-                float mm = 0.0f;
-#pragma unroll
-                for (int r = 0; r < KV; ++r) mm = fmaxf(mm, fabsf(v[r]));
-                wave_m = fmaxf(wave_m, mm);
+                group_max(abs_max(v), i);
             }
         }
     }
@@ -998,20 +1011,7 @@ struct Epilogue {
                 for (int k = 0; k < NBLK; ++k) store_group(a, t, row0, lane, i, k, grp(v, k));
             }
             if (!(want_abs || i8)) continue;
-            // rows past the grid are not part of the next operand; channels
-            // past cout neither
-            const bool blk_full = t.n0 + 16 * FN <= a.cout;
-            if (!valid[i] || !blk_full) {
-#pragma unroll
-                for (int k = 0; k < NBLK; ++k)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                            if (!valid[i] || ch >= a.cout) v[16 * k + 4 * jj + r] = 0.0f;
-                        }
-            }
+            drop_channels(v, t.n0);
             // channel order matters for the codes only
             if constexpr (E::NB == 128) {
                 if (i8) order128(v, std::true_type{});
@@ -1033,10 +1033,7 @@ struct Epilogue {
                     store_codes(w, i, k);
                 }
             } else {
-                float mm = 0.0f;
-#pragma unroll
-                for (int r = 0; r < V; ++r) mm = fmaxf(mm, fabsf(v[r]));
-                wave_m = fmaxf(wave_m, mm);
+                group_max(abs_max(v), i);
             }
         }
     }
@@ -1070,11 +1067,8 @@ struct Epilogue {
             }
         };
         if (f32 && !serial) load_factors();
-        // (the channel count is read once and the masks take no branch: with the
-        // argument read behind a lane's own condition, the compiler dropped the
-        // masked values of partly valid groups in one kernel)
-        const int cout = a.cout;
-        const bool blk_full = t.n0 + 64 * k + 64 <= cout;
+        const int c0 = t.n0 + 64 * k;
+        const bool blk_full = c0 + 64 <= a.cout;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             // The requantizing and absmax-only variants (the small-cin layer's
@@ -1109,23 +1103,8 @@ struct Epilogue {
                     quant16<kClamp>(v, qs, qr, q_fast, w);
                     store_codes(w, i, k);
                 } else {
-                    // the maximum of |z| over the valid pixels and channels
-                    // (wave-uniform branch: whole tiles take no masks)
-                    float mm = 0.0f;
-                    if (full && blk_full) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) mm = fmaxf(mm, fabsf(v[r]));
-                    } else {
-#pragma unroll
-                        for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                                const bool in = valid[i] & (ch < cout);
-                                mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
-                            }
-                    }
-                    wave_m = fmaxf(wave_m, mm);
+                    drop_channels(v, c0);
+                    group_max(abs_max(v), i);
                 }
                 continue;
             }
@@ -1145,30 +1124,11 @@ struct Epilogue {
             if (wh && (store || exact || i8)) fwht_acc<WB, true>(v, a.hblock);   // the column factors carry the 1/b
             if (store && valid[i]) store_group(a, t, row0, lane, i, k, v);
             if (NB == 1 && exact) {
-                // no transform: the maximum of |y| over the valid values
-                const bool all = full && blk_full;
-                float mm = 0.0f;
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                        const bool in = all | (valid[i] & (ch < cout));
-                        mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
-                    }
-                wave_m = fmaxf(wave_m, mm);
+                // no transform
+                drop_channels(v, c0);
+                group_max(abs_max(v), i);
             } else if (exact || i8) {
-                // Rows past the grid and channels past cout are not part of the
-                // next operand.
-                if (!full || !blk_full) {
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                            if (!valid[i] | (ch >= cout)) v[4 * jj + r] = 0.0f;
-                        }
-                }
+                drop_channels(v, c0);
                 if (i8) {
                     // codes of B_next y in channel order (restoring butterflies)
                     fwht_acc<NB, true>(v, a.next_hblock);
@@ -1176,7 +1136,7 @@ struct Epilogue {
                     quant16<kClamp>(v, qs, qr, q_fast, w);
                     store_codes(w, i, k);
                 } else {
-                    wave_m = fmaxf(wave_m, fwht_acc_absmax<NB>(v, a.next_hblock));
+                    group_max(fwht_acc_absmax<NB>(v, a.next_hblock), i);
                 }
             }
         }
