@@ -165,14 +165,24 @@ CONV = [  # (n, h, w, cin, cout, k, stride, pad, transposed, out_pad, form, hblo
     (1, 23, 17, 2, 128, 8, 2, 3, False, 0, "WH", 64),     # row-run, two K-steps
     (1, 21, 19, 3, 320, 5, 2, 2, False, 0, "WH", 64),     # row-run, 64-column tiles
     (1, 18, 22, 4, 64, 5, 2, 2, False, 0, "WH", 64),      # byte-gather path (20-byte runs)
-    (1, 30, 70, 192, 192, 4, 2, 1, False, 0, "DH", 64),   # LDS window path, k = 4
-    (1, 26, 40, 128, 192, 6, 2, 2, False, 0, "WH", 64),   # LDS window path, k = 6, two chunks
-    (2, 20, 21, 64, 192, 5, 2, 2, False, 0, "DH", 64),    # LDS window path, one chunk
+    (1, 30, 70, 192, 192, 4, 2, 1, False, 0, "DH", 64),   # small launch, k = 4
+    (1, 26, 40, 128, 192, 6, 2, 2, False, 0, "WH", 64),   # small launch, k = 6, two chunks
+    (2, 20, 21, 64, 192, 5, 2, 2, False, 0, "DH", 64),    # small launch, one chunk
     (150, 18, 18, 192, 192, 5, 2, 2, False, 0, "DH", 64), # 300 ragged tiles: blocks walk several, across samples
     (140, 17, 19, 192, 192, 5, 2, 2, False, 0, "WH", 64), # the same, WH
     (150, 18, 18, 64, 192, 5, 2, 2, False, 0, "DH", 64),  # one chunk, 300 tiles (the static tile order)
     (130, 17, 18, 192, 320, 5, 2, 2, False, 0, "WH", 64), # 320 columns: two launches (192 + 128), 260 tiles each
-    (3, 21, 30, 192, 320, 5, 2, 2, False, 0, "DH", 64),   # the same split with the DH epilogues
+    (3, 21, 30, 192, 320, 5, 2, 2, False, 0, "DH", 64),   # small launch, 320 columns, DH
+    # launches that the kernels of small ones do not take
+    (110, 18, 20, 192, 192, 4, 2, 1, False, 0, "DH", 64), # LDS window path, k = 4
+    (110, 17, 20, 128, 192, 6, 2, 2, False, 0, "WH", 64), # LDS window path, k = 6, two chunks
+    (130, 17, 18, 64, 320, 5, 2, 2, False, 0, "DH", 64),  # 320 columns in two launches, DH
+    (140, 5, 9, 192, 192, 1, 1, 0, False, 0, "WH", 64),   # 1x1 on the pipeline kernel
+    (1, 9, 20, 704, 64, 5, 1, 2, False, 0, "WH", 64),     # 275 steps: the pipeline kernel's 64,
+    (1, 9, 20, 704, 192, 5, 1, 2, False, 0, "DH", 64),    # 192
+    (1, 9, 20, 704, 320, 5, 1, 2, False, 0, "WH", 64),    # and 320 columns, stride 1
+    (1, 5, 9, 1088, 192, 8, 2, 3, True, 0, "DH", 64),     # 272 steps per transposed phase
+    (1, 4, 7, 1088, 128, 8, 2, 3, True, 1, "WH", 16),
 ]
 CONV_IDS = [f"n{c[0]}-{c[1]}x{c[2]}-{c[3]}to{c[4]}-k{c[5]}s{c[6]}-{c[10]}{'-T' if c[8] else ''}" for c in CONV]
 

@@ -156,6 +156,42 @@ def test_reduction_block_sizes(shape, b):
     assert bool((qa.amax(dim=(1, 2, 3)) >= 126).all()) and bool((qa.amin(dim=(1, 2, 3)) <= -127).all())
 
 
+# The transformed maxima of the large-block reductions, exactly: small whole numbers
+# (every partial sum of the transform is exact in fp32), the transform a float64
+# product by the order's matrix, samples of more than 16384 items (blocks of 1024
+# threads, 512 for the order 320) and of fewer, and the largest positive and negative
+# values in the first item, the last and one in between.
+@pytest.mark.parametrize("b,pixels", [(16, 4133), (64, 16801), (128, 17419), (192, 16567), (320, 16453),
+                                      (64, 5003), (128, 1201), (192, 2503), (320, 907)])
+@pytest.mark.parametrize("n", [1, 3])
+def test_reductions_transformed(orc, b, pixels, n):
+    c = 64 * 5 if b == 16 else b
+    H = torch.from_numpy(orc.activation_transform(np.eye(b, dtype=np.float32).reshape(1, 1, b, b), b)
+                         .reshape(b, b).astype(np.float64)).cuda()   # row i: the transform of unit vector i
+    g = torch.Generator("cuda").manual_seed(21)
+    base = torch.randint(-3, 4, (n, 1, pixels, c), device="cuda", generator=g).float()
+    items = pixels * c // b
+    for hi, lo in ((0, items - 1), (items - 1, 0), (items // 2 + 1, items // 3), (items - 2, 1)):
+        x = base.clone()
+        flat = x.view(n, items, b)
+        for i in range(n):   # aligned with a row of the transform: b times the entry's size
+            col = (5 * i + 3) % b
+            flat[i, hi] = 20.0 * torch.sign(H[:, col]).float()
+            flat[i, lo] = -17.0 * torch.sign(H[:, col]).float()
+        S = (x.view(-1, b).double() @ H).view(n, -1)
+        am = S.abs().amax(1).float()
+        assert torch.equal(am.double(), S.abs().amax(1)) and int((S.abs() == S.abs().amax(1, True)).sum()) == n
+        amax, _ = hatq.hatq_range_expansion(x, b)
+        assert torch.equal(amax[n:], am) and torch.equal(amax[:n], x.abs().amax(dim=(1, 2, 3)))
+        q, s = hatq.hatq_fwht_quant_act(x, b)
+        assert torch.equal(s, am / torch.full((1,), 127.0, device="cuda"))
+        qa, sa, za = hatq.hatq_fwht_quant_act_affine(x, b)
+        top, bot = S.amax(1).float(), (-S).amax(1).float()
+        want = (top + bot) / torch.full((1,), 255.0, device="cuda")
+        assert torch.equal(sa, want)
+        assert torch.equal(za, (torch.round(bot / want) - 128).clamp(-128, 127).int())
+
+
 # Orders that span a layer's columns (192, 320): many small samples (the large-launch
 # kernels) against few of them (the kernel of small launches on all columns).
 @pytest.mark.parametrize("cout,form,hb,nb", [(192, "DH", 64, 192), (192, "WH", 192, 192), (192, "WH", 192, 1),
