@@ -470,7 +470,7 @@ struct Epilogue {
     const int row0, lane, p, q;
     const float *col_t, *col_b;
     const EpiFlags<E> fl;
-    bool z_bound, zpair, q_fast, kron;
+    bool full, z_bound, zpair, q_fast, kron;
     float wave_m, seen, qs, qr;
     int nbk, rq_n, rq_pre, zp;
     int64_t rq_bias;
@@ -484,6 +484,8 @@ struct Epilogue {
                                         const int32_t *tot_ = nullptr, const int32_t *taps_ = nullptr)
         : a(a_), t(t_), row0(row0_), lane(lane_), p(lane_ & 15), q(lane_ >> 4), col_t(col_t_), col_b(col_b_),
           fl(a_), slot(slot_), tot(tot_), taps(taps_) {
+        // the whole tile inside the grid (wave-uniform): no row masking needed
+        full = t.gi0 + (row0 + 16 * FM - 1) / TW < a.gh && t.gj0 + TW <= a.gw;
         wave_m = 0.0f;
         nbk = generic ? a.next_hblock : NB;
         // WH layer whose next operand uses the same blocks, with the paired
@@ -735,28 +737,14 @@ struct Epilogue {
         }
     }
 
-    // What is not part of the next operand.  Pixels past the grid: the transforms
-    // meet the lanes of one pixel only and codes are stored where valid, so it is
-    // enough that such a lane's maximum does not count.  Channels past cout (the
-    // padding of a WH layer's last block), which do mix: zeroed before the
-    // transform; v[4 jj + r] is channel c0 + 16 jj + 4 q + r.
-    __device__ __forceinline__ void group_max(float mm, int i) {
-        wave_m = fmaxf(wave_m, valid[i] ? mm : 0.0f);
-    }
-    template <int N>
-    __device__ __forceinline__ void drop_channels(float (&v)[N], int c0) const {
-        if (c0 + 4 * N <= a.cout) return;   // wave-uniform
-        const int left = a.cout - c0 - 4 * q;
-#pragma unroll
-        for (int e = 0; e < N; ++e) v[e] = 16 * (e / 4) + e % 4 < left ? v[e] : 0.0f;
-    }
-    template <int N>
-    static __device__ __forceinline__ float abs_max(const float (&v)[N]) {
-        float mm = 0.0f;
-#pragma unroll
-        for (int e = 0; e < N; ++e) mm = fmaxf(mm, fabsf(v[e]));
-        return mm;
-    }
+    // Whether channel ch of row group i's pixel is not part of the next operand: a pixel
+    // past the grid or a channel past cout (the padding of a WH layer's last block).
+    // Every order masks by this, behind a wave-uniform condition, with the channel
+    // count read before the row groups and without a branch: read behind a lane's own
+    // condition, the compiler lost masked values of partly valid groups in one kernel.
+    // (Dropping the lane's maximum instead of zeroing its values is slower on tiles
+    // that reach past the grid: 1x1 64 -> 192, (16, 63, 60), 25 -> 30 us.)
+    __device__ __forceinline__ bool outside(int i, int ch, int cout) const { return !valid[i] | (ch >= cout); }
 
     // The sixteen values of 64-channel block k among a row group's KV.
     template <typename T>
@@ -836,8 +824,13 @@ struct Epilogue {
                 for (int k = 0; k < NBLK; ++k) store_group(a, t, row0, lane, i, k, grp(v, k));
             }
             if (!(want_abs || i8)) continue;
-            // (cout is a multiple of the next block: every channel is part of the
-            // next operand.)  Channel order matters for the codes only.
+            // (cout is a multiple of the next block: every channel counts)
+            if (!full) {
+#pragma unroll
+                for (int r = 0; r < KV; ++r)
+                    if (outside(i, 0, 1)) v[r] = 0.0f;
+            }
+            // channel order matters for the codes only
             auto next_kron = [&]() {
                 if (i8) {
 #pragma unroll
@@ -879,7 +872,10 @@ struct Epilogue {
                     store_codes(w, i, k);
                 }
             } else {
-                group_max(abs_max(v), i);
+                float mm = 0.0f;
+#pragma unroll
+                for (int r = 0; r < KV; ++r) mm = fmaxf(mm, fabsf(v[r]));
+                wave_m = fmaxf(wave_m, mm);
             }
         }
     }
@@ -969,6 +965,8 @@ struct Epilogue {
     // ascending stage order).
     __device__ void block_s128(const v4i (&acc)[FM][FN]) {
         constexpr int V = 4 * FN;
+        const int cout = a.cout;
+        const bool blk_full = t.n0 + 16 * FN <= cout;
         const bool want_abs = fl.want_abs, i8 = fl.i8, store = fl.store;
         auto order128 = [](float (&v)[V], auto RESTOREc) {
             constexpr bool RESTORE = decltype(RESTOREc)::value;
@@ -1011,7 +1009,17 @@ struct Epilogue {
                 for (int k = 0; k < NBLK; ++k) store_group(a, t, row0, lane, i, k, grp(v, k));
             }
             if (!(want_abs || i8)) continue;
-            drop_channels(v, t.n0);
+            if (!full || !blk_full) {
+#pragma unroll
+                for (int k = 0; k < NBLK; ++k)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
+                            if (outside(i, ch, cout)) v[16 * k + 4 * jj + r] = 0.0f;
+                        }
+            }
             // channel order matters for the codes only
             if constexpr (E::NB == 128) {
                 if (i8) order128(v, std::true_type{});
@@ -1033,7 +1041,10 @@ struct Epilogue {
                     store_codes(w, i, k);
                 }
             } else {
-                group_max(abs_max(v), i);
+                float mm = 0.0f;
+#pragma unroll
+                for (int r = 0; r < V; ++r) mm = fmaxf(mm, fabsf(v[r]));
+                wave_m = fmaxf(wave_m, mm);
             }
         }
     }
@@ -1067,8 +1078,8 @@ struct Epilogue {
             }
         };
         if (f32 && !serial) load_factors();
-        const int c0 = t.n0 + 64 * k;
-        const bool blk_full = c0 + 64 <= a.cout;
+        const int cout = a.cout;
+        const bool blk_full = t.n0 + 64 * k + 64 <= cout;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             // The requantizing and absmax-only variants (the small-cin layer's
@@ -1103,8 +1114,23 @@ struct Epilogue {
                     quant16<kClamp>(v, qs, qr, q_fast, w);
                     store_codes(w, i, k);
                 } else {
-                    drop_channels(v, c0);
-                    group_max(abs_max(v), i);
+                    // the maximum of |z| over the valid pixels and channels
+                    // (wave-uniform branch: whole tiles take no masks)
+                    float mm = 0.0f;
+                    if (full && blk_full) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) mm = fmaxf(mm, fabsf(v[r]));
+                    } else {
+#pragma unroll
+                        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
+                                const bool in = !outside(i, ch, cout);
+                                mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
+                            }
+                    }
+                    wave_m = fmaxf(wave_m, mm);
                 }
                 continue;
             }
@@ -1124,11 +1150,30 @@ struct Epilogue {
             if (wh && (store || exact || i8)) fwht_acc<WB, true>(v, a.hblock);   // the column factors carry the 1/b
             if (store && valid[i]) store_group(a, t, row0, lane, i, k, v);
             if (NB == 1 && exact) {
-                // no transform
-                drop_channels(v, c0);
-                group_max(abs_max(v), i);
+                // no transform: the maximum of |y| over the valid values
+                const bool all = full && blk_full;
+                float mm = 0.0f;
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
+                        const bool in = all | !outside(i, ch, cout);
+                        mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
+                    }
+                wave_m = fmaxf(wave_m, mm);
             } else if (exact || i8) {
-                drop_channels(v, c0);
+                // Rows past the grid and channels past cout are not part of the
+                // next operand.
+                if (!full || !blk_full) {
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
+                            if (outside(i, ch, cout)) v[4 * jj + r] = 0.0f;
+                        }
+                }
                 if (i8) {
                     // codes of B_next y in channel order (restoring butterflies)
                     fwht_acc<NB, true>(v, a.next_hblock);
@@ -1136,7 +1181,7 @@ struct Epilogue {
                     quant16<kClamp>(v, qs, qr, q_fast, w);
                     store_codes(w, i, k);
                 } else {
-                    group_max(fwht_acc_absmax<NB>(v, a.next_hblock), i);
+                    wave_m = fmaxf(wave_m, fwht_acc_absmax<NB>(v, a.next_hblock));
                 }
             }
         }
