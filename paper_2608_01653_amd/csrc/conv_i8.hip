@@ -4103,22 +4103,49 @@ hipError_t conv_part_win_wide(const ConvArgs &a, bool *hit, hipStream_t st) {
 //  * stride 1 and transposed (conv_pipe_kernel, four phase launches for the
 //    latter): b4 192 166/15/16, 960 184/33/26, 5292 134/91/80, 12672 222/156/109,
 //    19872 258/275/209; 3x3 70 15/10/12, 1188 35/20/19, 3276 68/47/41.
-//  * 1x1, too few steps to hide a block's start and end: b4 64 24/7/9, 819
+//  * stride 2, k < 4: few steps per window (k = 1 loads four times the pixels it
+//    needs), so the general kernel catches up sooner, above all where it has the
+//    epilogue at compile time (192 and 320 columns).  b8, old / this: those, fp32 output,
+//    k = 1, 64 -> 192 480 12/10, 768 12/14, 1536 15/23; 192 -> 192 360 13/12, 576 14/19;
+//    k = 2, 64 -> 192 663 15/13, 1326 17/22; 192 -> 320 910 33/31, 1105 23/29; k = 3,
+//    64 -> 192 1536 24/26, 1740 38/30, 64 -> 320 with maxima 1625 57/42, 3840 69/72, 192
+//    -> 320 3840 115/109, 11520 322/353.  k = 1 otherwise: integer codes 64 -> 320 1760
+//    35/30, 2560 37/39, 192 -> 320 600 21/19, 2560 40/53, 192 -> 256 1120 44/35, 2944
+//    66/80; tiles of 64 columns, 64 -> 64 fp32 493 17/11, accumulators 64 -> 448 252 7/7,
+//    960 14/21; fp32 320 -> 448 448 10/12.
+//  * 1x1 stride 1, too few steps to hide a block's start and end: b4 64 24/7/9, 819
 //    19/20/18, 1590 11/19/16, 2880 16/30/23 at 192 and 320 columns; the other
-//    widths, whose general kernel has run-time epilogues only, 2040 44/32/32,
-//    4620 58/58/51.
+//    widths, whose general kernel has run-time epilogues only, fp32 with maxima b8 288
+//    18/18/15, 384 21/18/15, 1536 43/38/30; accumulators 64 -> 448 224 6/7/8, 588
+//    13/16/15, 128 -> 448 2800 36/51/40, 192 -> 448 1008 21/22/17.
 static int win_rows(const ConvArgs *p, int nph) {
     const ConvArgs &a = p[0];
     if (a.cin_p % 64 || a.cout_pad % 64 || a.sa > 2) return 0;
     const int64_t cols = (int64_t)a.n * ((a.gw + 15) / 16) * (a.cout_pad / 64) * nph;
     const int64_t b4 = cols * ((a.gh + 3) / 4), b8 = cols * ((a.gh + 7) / 8);
     const bool wide = a.cout_pad == 192 || a.cout_pad == 320;
+    const bool tile64 = !wide && a.cout_pad != 128 && a.cout_pad != 256;   // 64 columns per general tile
     if (a.sa == 2) {
+        // the epilogues that the general kernel has at compile time for these widths
+        const bool fixed = wide && (epi_matches<Epi<0, 64>>(a) || epi_matches<Epi<0, 1>>(a) || epi_matches<Epi<0, 0>>(a) ||
+                                    epi_matches<Epi<64, 64>>(a) || epi_matches<Epi<64, 1>>(a) || epi_matches<Epi<64, 0>>(a));
+        if (a.k == 1) {
+            const bool codes = a.mode == kModeIntTransition, one = a.cin_p == 64;
+            const int most = fixed    ? 480
+                             : wide   ? !codes ? INT32_MAX : one ? 2000 : 800
+                             : tile64 ? one && a.mode != 0 ? 700 : 250
+                                      : codes ? 900 : INT32_MAX;
+            if (b8 > most) return 0;
+        }
         if (b4 <= 600) return 4;
-        return !wide || a.k < 4 || b8 <= (a.cout_pad == 192 ? 600 : 1000) ? 8 : 0;
+        if (!wide) return 8;
+        if (a.k < 4) return !fixed || b8 <= (a.k < 3 ? 900 : a.cin_p == 64 ? 3000 : 6000) ? 8 : 0;
+        return b8 <= (a.cout_pad == 192 ? 600 : 1000) ? 8 : 0;
     }
-    if (b4 <= (a.ntaps > 1 ? 500 : 800)) return 4;
-    return a.ntaps > 1 || !wide ? 8 : 0;
+    if (b4 <= (a.ntaps > 1 ? 500 : nph > 1 ? 800 : 512)) return 4;
+    if (nph > 1 || a.ntaps > 1) return 8;
+    if (wide) return b4 <= 800 ? 8 : 0;
+    return a.mode == 0 && a.cin_p <= 128 && tile64 && b8 > 300 ? 0 : 8;
 }
 
 // Whether conv_cols_kernel takes the launch: stride 1 and transposed, at least

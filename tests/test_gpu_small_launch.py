@@ -71,6 +71,11 @@ BATCH = [
     (9, 17, 64, 192, 3, 1, 1, False, 0, "DH", 64),     # three units
     (9, 17, 64, 320, 3, 1, 1, False, 0, "WH", 64),     # five units: some waves take two
     (9, 17, 64, 256, 1, 1, 0, False, 0, "DH", 64),
+    (9, 17, 64, 192, 1, 2, 0, False, 0, "WH", 64),     # stride 2, k < 4: back to the large kernels sooner
+    (9, 17, 128, 128, 1, 2, 0, False, 0, "DH", 64),
+    (9, 17, 64, 320, 2, 2, 0, False, 0, "DH", 64),
+    (9, 17, 64, 192, 3, 2, 1, False, 0, "WH", 64),
+    (9, 17, 64, 64, 1, 1, 0, False, 0, "WH", 16),
 ]
 
 
@@ -91,7 +96,8 @@ def test_launch_sizes_agree(c, next_b):
         y = hatq.hatq_conv_int8(layer, q, sc, hatq.HATQ_OUT_F32, next_hblock=next_b, next_absmax=m)
         yq, sq = hatq.hatq_conv_int8_requant(layer, q, sc, next_b, next_absmax=m)
         t, _ = hatq.hatq_int_transition_params(layer, 1.0, 4000.0, next_b)
-        return [m, y, yq, sq, hatq.hatq_conv_int8_int_transition(layer, q, next_b, t)]
+        return [m, y, yq, sq, hatq.hatq_conv_int8_int_transition(layer, q, next_b, t),
+                hatq.hatq_conv_int8(layer, q, sc, hatq.HATQ_OUT_I32)]
 
     big = run(xq, sx)
     for i, cnt in ((0, 1), (7, 60), (300, 120)):
