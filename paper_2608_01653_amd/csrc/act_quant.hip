@@ -17,6 +17,7 @@
 // When the producer of x already computed A (next_absmax of the convolution),
 // only quant_kernel runs and x is read once.
 #include <mutex>
+#include <type_traits>
 
 #include "hatq_device.h"
 #include "hatq_launch.h"
@@ -57,36 +58,27 @@ __device__ __forceinline__ void load_item(const float *xs, int64_t base, int64_t
 }
 
 // The reductions (absmax, min/max, range): blocks of RT threads, f(item) for
-// every item of a sample the quad takes, from the sample's end, its values in
-// registers; the loads of two items are issued before the first is used (one of
-// the widest orders).  Their blocks end in one atomic per value on an address
-// that all blocks of a sample share (or its slots), some 7 ns each, one after the
-// other: at most kRedGrid blocks of 1024 threads (two per CU) instead of up to 4096
-// of 256.  Range pass of one 50 MB sample 35 -> 17 us, of 151 MB in two 42 -> 30,
-// 604 MB in eight 105 -> 106; absmax pass of 50 MB 23 -> 11 us.  Small samples keep
-// blocks of 256 threads (2 MB: range 8.1 us, 9.4 with 16 blocks of 1024).
-constexpr int kRedGrid = 512;
-// (the order 320, 80 values per lane: 512 threads, as 128 registers spill)
-template <int B>
-constexpr int red_threads = B > 192 ? 512 : 1024;
-constexpr int64_t kRedSmallItems = 16384;
-
-template <int B, int RT, typename F>
+// every item of a sample the quad takes, its values in registers; the loads of U items
+// are issued before the first is used.  From the sample's end (FWD: from its
+// beginning); launch shapes below.
+template <int B, int RT, int U, bool FWD, typename F>
 __device__ __forceinline__ void for_items(const float *xs, int64_t E, int t, F &&f) {
-    constexpr int I = ItemShape<B>::I, R = ItemShape<B>::R, U = B <= 128 ? 2 : 1;
+    constexpr int I = ItemShape<B>::I, R = ItemShape<B>::R;
     const int64_t items = (E + I - 1) / I, step = (int64_t)gridDim.x * (RT / 4);
     int64_t it = (int64_t)blockIdx.x * (RT / 4) + (threadIdx.x >> 2);
     for (; it + (U - 1) * step < items; it += U * step) {
         float v[U][4 * R];
 #pragma unroll
-        for (int u = 0; u < U; ++u) load_item<B>(xs, (items - 1 - it - u * step) * I, E, t, v[u]);
+        for (int u = 0; u < U; ++u) load_item<B>(xs, (FWD ? it + u * step : items - 1 - it - u * step) * I, E, t, v[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u) f(v[u]);
     }
-    for (; it < items; it += step) {
-        float v[4 * R];
-        load_item<B>(xs, (items - 1 - it) * I, E, t, v);
-        f(v);
+    if constexpr (U > 1) {
+        for (; it < items; it += step) {
+            float v[4 * R];
+            load_item<B>(xs, (FWD ? it : items - 1 - it) * I, E, t, v);
+            f(v);
+        }
     }
 }
 
@@ -96,10 +88,14 @@ __device__ __forceinline__ void for_items(const float *xs, int64_t E, int t, F &
 template <int RT, int N>
 __device__ __forceinline__ void block_max(const float (&m)[N], float *const (&out)[N], bool own = false) {
     __shared__ float red[N][RT / 64];
+    // (the values' lane exchanges side by side: one after the other they were 0.3 us
+    // of a small launch)
+    float wm[N];
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const float w = wave_max(m[k]);
-        if ((threadIdx.x & 63) == 0) red[k][threadIdx.x >> 6] = w;
+    for (int k = 0; k < N; ++k) wm[k] = wave_max(m[k]);
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) red[k][threadIdx.x >> 6] = wm[k];
     }
     __syncthreads();
     if (threadIdx.x < N) {
@@ -122,14 +118,14 @@ __device__ __forceinline__ float slots_max(const float *p, int slots) {
     return wave_max(lane < slots ? p[lane] : 0.0f);
 }
 
-template <int B, int RT>
+template <int B, int RT, int U, bool FWD>
 __global__ void __launch_bounds__(RT) absmax_kernel(const float *__restrict__ x, int64_t E,
                                                     float *__restrict__ absmax, int own) {
     // from the end of the batch: the codes pass then reads from its beginning,
     // where this pass's last reads are still in the 256 MB memory-side cache
-    const int n = gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
+    const int n = FWD ? blockIdx.y : gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
     float m[1] = {0.0f};
-    for_items<B, RT>(x + (int64_t)n * E, E, t, [&](auto &v) {
+    for_items<B, RT, U, FWD>(x + (int64_t)n * E, E, t, [&](auto &v) {
         fwht_item<B>(v, t);
 #pragma unroll
         for (float e : v) m[0] = fmaxf(m[0], fabsf(e));
@@ -307,12 +303,12 @@ __global__ void __launch_bounds__(kThreads) quant_kernel(const float *__restrict
 // ---- affine quantization (Eq. affine_q, Eq. uniform_q) ----------------------
 // Signed grid [-128, 127].  amax[k] = max(max S, 0), amax[n + k] = max(-min S, 0)
 // (both non-negative, so the order-preserving atomic serves both).
-template <int B, int RT>
+template <int B, int RT, int U, bool FWD>
 __global__ void __launch_bounds__(RT) minmax_kernel(const float *__restrict__ x, int64_t E,
-                                                    float *__restrict__ amax, int slots) {
-    const int k = gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
+                                                    float *__restrict__ amax) {
+    const int k = FWD ? blockIdx.y : gridDim.y - 1 - blockIdx.y, t = threadIdx.x & 3;
     float m[2] = {0.0f, 0.0f};   // max(S, 0) and max(-S, 0)
-    for_items<B, RT>(x + (int64_t)k * E, E, t, [&](auto &v) {
+    for_items<B, RT, U, FWD>(x + (int64_t)k * E, E, t, [&](auto &v) {
         const float sigma = fwht_item<B>(v, t);
 #pragma unroll
         for (float e : v) {
@@ -321,8 +317,7 @@ __global__ void __launch_bounds__(RT) minmax_kernel(const float *__restrict__ x,
             m[1] = fmaxf(m[1], -sv);
         }
     });
-    float *dst = amax + (int64_t)k * slots + blockIdx.x % slots;
-    block_max<RT, 2>(m, {dst, dst + (int64_t)gridDim.y * slots});
+    block_max<RT, 2>(m, {amax + k, amax + gridDim.y + k});
 }
 
 // s = fl32(fl32(hi + lo) / 255) and z = clamp(rne(fl32(lo / s)) - 128) for a
@@ -343,7 +338,7 @@ template <int B>
 __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__restrict__ x, int64_t E,
                                                                 const float *__restrict__ amax,
                                                                 int8_t *__restrict__ xq, float *__restrict__ act_scale,
-                                                                int32_t *__restrict__ act_zero, int slots) {
+                                                                int32_t *__restrict__ act_zero) {
     constexpr int I = ItemShape<B>::I;
     constexpr int R = ItemShape<B>::R;
     const int k = blockIdx.y;
@@ -352,8 +347,7 @@ __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__r
     const int t = threadIdx.x & 3;
     float s;
     int z;
-    affine_params(slots_max(amax + (int64_t)k * slots, slots), slots_max(amax + ((int64_t)gridDim.y + k) * slots, slots),
-                  s, z);
+    affine_params(amax[k], amax[gridDim.y + k], s, z);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         act_scale[k] = s;
         act_zero[k] = z;
@@ -385,12 +379,12 @@ __global__ void __launch_bounds__(kThreads) quant_affine_kernel(const float *__r
 // ---- range-expansion profiling (Eq. hadamard_sensitivity) -------------------
 // One read of x gives both maxima of each sample: max |x| (into amax[k]) and
 // max |S| of the same butterfly the quantizer applies (into amax[n + k]).
-template <int B, int RT>
+template <int B, int RT, int U>
 __global__ void __launch_bounds__(RT) range_kernel(const float *__restrict__ x, int64_t E,
                                                    float *__restrict__ amax) {
     const int k = blockIdx.y, t = threadIdx.x & 3;
     float m[2] = {0.0f, 0.0f};   // max |x| and max |S|
-    for_items<B, RT>(x + (int64_t)k * E, E, t, [&](auto &v) {
+    for_items<B, RT, U, false>(x + (int64_t)k * E, E, t, [&](auto &v) {
 #pragma unroll
         for (float e : v) m[0] = fmaxf(m[0], fabsf(e));
         fwht_item<B>(v, t);
@@ -514,41 +508,105 @@ int grid_x(int64_t work_units, int per_block, int n, int total = HATQ_QUANT_GRID
     return (int)(want < 1 ? 1 : want);
 }
 
-// A sample of at most kOwnFloats floats goes to at most kAbsSlots blocks, each with a
-// slot of its own: the slots need no clearing, one launch less (1-2 us on the GPU
-// and as much on the host).  Two-pass time without / with: order 64, 0.6 M floats 11.0 /
-// 10.0 us, 1.2 M 11.3 / 11.8; untransformed 1.2 M 10.9 / 9.8.
-template <int B>
-constexpr int64_t kOwnFloats = (int64_t)1 << (B == 1 ? 21 : 20);
+// Launch shapes of the reductions.  They are bound by memory, or, for small samples,
+// by their start and end: the blocks end in one atomic per value on an address that
+// all blocks of a sample share (or its slots), some 7 ns each, one after the other.
+// So up to order 128 at most 512 blocks of 1024 threads (two per CU) over the batch;
+// with up to 4096 blocks of 256 (2048 for min/max and range) the range pass of one 50 MB
+// sample of order 64 took 33 us, now 17, the absmax and codes passes 37, now 25.  Small
+// samples take fewer threads: range of 3.1 MB 8.4 (256), 7.5 (512), 7.6 us (1024).  The
+// orders 192 and 320 (48 and 80 values per lane) hold fewer waves per CU, and with 1024
+// threads most of them wait for the slowest: absmax and codes of order 192, 12.6 MB, 15.0
+// (256), 15.6 (512), 18.0 us (1024), 64 samples of 1.8 MB 56 / 57 / 67; order 320, 32
+// samples of 2.9 MB 65 / 75 / 81.
+// Blocks per sample: one per RT / 4 items, `total` over the whole batch at most, none
+// left over for a round of their own (513 blocks of order 128 over three samples of
+// 98 MB: range 61 us, 510: 57).
+constexpr int kRedGrid = 512;
+int red_blocks(int64_t work_units, int per_block, int n, int total = kRedGrid) {
+    const int64_t want = (work_units + per_block - 1) / per_block, cap = total / n > 0 ? total / n : 1;
+    return (int)(want < 1 ? 1 : want < cap ? want : cap);
+}
 
-template <int B, int RT>
+// The reduction before a codes pass of an order of 192 or 320, a batch that fits the
+// XCDs' L2s: blocks of 256 threads from the beginning, as the codes pass has them, so
+// that each block finds its items in its own L2 (order 192, 24 MB: 20 us, 22-23 with
+// any other shape; up to order 128 the shapes above are faster, 20 against 16).
+template <int B>
+bool red_mapped(int n, int64_t E) {
+    return B > 128 && (int64_t)n * E <= (int64_t)7 << 20;
+}
+
+// The minimum and maximum or range pass: f(threads, U, FWD) and the blocks per sample.
+template <int B, typename F>
+void red_launch(int n, int64_t items, bool mapped, F &&f) {
+    using std::integral_constant;
+    constexpr integral_constant<int, 1> one{};
+    constexpr integral_constant<int, 2> two{};
+    constexpr std::true_type fwd{};
+    constexpr std::false_type rev{};
+    if constexpr (B <= 128) {
+        if (items < 16384) {
+            constexpr int RT = B == 128 ? 256 : 512;
+            // (many samples, whose maxima lie on several cache lines: more blocks)
+            const int blocks = red_blocks(items, RT / 4, n, n < 128 ? kRedGrid : 1024 * 1024 / RT);
+            if ((int64_t)blocks * (RT / 4) >= items) f(integral_constant<int, RT>{}, one, rev, blocks);
+            else f(integral_constant<int, RT>{}, two, rev, blocks);
+        } else {
+            f(integral_constant<int, 1024>{}, two, rev, red_blocks(items, 256, n));
+        }
+    } else {
+        if (mapped) f(integral_constant<int, 256>{}, one, fwd, red_blocks(items, 64, n, 1 << 20));
+        else if (B == 192 && items >= 12288) f(integral_constant<int, 512>{}, one, rev, red_blocks(items, 128, n));
+        else f(integral_constant<int, 256>{}, one, rev, red_blocks(items, 64, n));
+    }
+}
+
+// A sample of few floats goes to at most kAbsSlots blocks, each with a slot of its
+// own: the slots need no clearing, one launch less (1-2 us on the GPU and as much on
+// the host).  Order 64, 0.8 MB 8.4 us without, 6.7 with, 3.1 MB 9.0 / 8.4, 7.1 MB 10.2 /
+// 11.3; untransformed 9.4 MB 10.0 / 9.4; order 320, 1.3 MB 20.4 / 18.7, 32 samples of 2.9
+// MB 65 / 72.
+template <int B>
+bool red_own(int n, int64_t E) {
+    return E <= (B == 1 ? 1 << 21 : B <= 192 || n < 16 ? 1 << 20 : 3 << 17);
+}
+
+template <int B, int RT, bool FWD = false>
 void launch_absmax(const float *x, int n, int64_t E, float *ws, int blocks, int own, hipStream_t st) {
     if constexpr (B == 1) absmax_flat_kernel<RT><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws, own);
-    else absmax_kernel<B, RT><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws, own);
+    else absmax_kernel<B, RT, B <= 128 ? 2 : 1, FWD><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws, own);
 }
 
 template <int B>
 hipError_t launch_vector(const float *x, int n, int64_t E, const float *absmax_in, float *ws_absmax,
                          int8_t *xq, float *act_scale, hipStream_t st, int c64 = 0) {
-    constexpr int I = ItemShape<B>::I, RT = red_threads<B>;
+    constexpr int I = ItemShape<B>::I;
     const int64_t items = (E + I - 1) / I;
     const float *A = absmax_in;
     int slots = 1;
-    if (!A && E <= kOwnFloats<B>) {
-        // blocks of 256 threads while a quad has at most two items
-        const bool small = items <= 2 * 64 * kAbsSlots;
-        const int64_t want = (items + (small ? 64 : RT / 4) - 1) / (small ? 64 : RT / 4);
-        slots = (int)(want < kAbsSlots ? want : kAbsSlots);
-        if (small) launch_absmax<B, 256>(x, n, E, ws_absmax, slots, 1, st);
-        else launch_absmax<B, RT>(x, n, E, ws_absmax, slots, 1, st);
+    if (!A && red_own<B>(n, E)) {
+        // a quad with at most two items (four of order 320, whose blocks of more threads
+        // do not pay): fewer threads
+        const bool few = items <= (B == 192 ? 2048 : 2 * 64 * kAbsSlots);
+        constexpr int SMALL = B <= 64 ? 512 : 256, LARGE = B <= 128 ? 1024 : B == 192 ? 512 : 256;
+        slots = red_blocks(items, (few ? SMALL : LARGE) / 4, 1, kAbsSlots);
+        if (few) launch_absmax<B, SMALL>(x, n, E, ws_absmax, slots, 1, st);
+        else launch_absmax<B, LARGE>(x, n, E, ws_absmax, slots, 1, st);
         A = ws_absmax;
     } else if (!A) {
         slots = kAbsSlots;
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws_absmax), n * kAbsSlots, 0u);
-        // (the untransformed pass, with the fewest registers: twice the blocks, four
-        // float4 per thread at least)
-        const int blocks = B == 1 ? grid_x(E / 4, RT * 4, n, 2 * kRedGrid) : grid_x(items, RT / 4, n, kRedGrid);
-        launch_absmax<B, RT>(x, n, E, ws_absmax, blocks, 0, st);
+        if constexpr (B == 1)   // (with the fewest registers: twice the blocks, four float4 per thread at least)
+            launch_absmax<B, 1024>(x, n, E, ws_absmax, red_blocks(E / 4, 4096, n, 2 * kRedGrid), 0, st);
+        else if constexpr (B <= 128)
+            launch_absmax<B, 1024>(x, n, E, ws_absmax, red_blocks(items, 256, n), 0, st);
+        else if (red_mapped<B>(n, E))
+            launch_absmax<B, 256, true>(x, n, E, ws_absmax, red_blocks(items, 64, n, 1 << 20), 0, st);
+        else if constexpr (B == 192)
+            launch_absmax<B, 512>(x, n, E, ws_absmax, red_blocks(items, 128, n, 2 * kRedGrid), 0, st);
+        else
+            launch_absmax<B, 256>(x, n, E, ws_absmax, red_blocks(items, 64, n, 8 * kRedGrid), 0, st);
         A = ws_absmax;
     }
     dim3 grid(grid_x(items, kQuadsPerBlock * QuantUnroll<B>::UN, n), n);
@@ -577,10 +635,10 @@ hipError_t launch_range_b(const float *x, int n, int64_t P, int C, float *amax, 
     if (C % B == 0 && E % 4 == 0) {
         constexpr int I = ItemShape<B>::I;
         const int64_t items = (E + I - 1) / I;
-        if (items < kRedSmallItems)
-            range_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, amax);
-        else
-            range_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, amax);
+        red_launch<B>(n, items, false, [&](auto rt, auto u, auto, int blocks) {
+            constexpr int RT = decltype(rt)::value;
+            range_kernel<B, RT, decltype(u)::value><<<dim3(blocks, n), RT, 0, st>>>(x, E, amax);
+        });
     } else if constexpr (kron_q(B) == 0) {
         const int64_t units = P * ((C + B - 1) / B);
         range_pad_kernel<B><<<dim3(grid_x(units, kThreads, n, 2048), n), kThreads, 0, st>>>(x, P, C, amax);
@@ -592,20 +650,16 @@ hipError_t launch_range_b(const float *x, int n, int64_t P, int C, float *amax, 
 
 template <int B>
 hipError_t launch_affine_b(const float *x, int n, int64_t E, float *ws, int8_t *xq, float *act_scale,
-                           int32_t *act_zero, bool spread, hipStream_t st) {
+                           int32_t *act_zero, hipStream_t st) {
     constexpr int I = ItemShape<B>::I;
     const int64_t items = (E + I - 1) / I;
-    // the documented workspace is a multiple of 256 bytes: what is left of 64
-    // floats per batch spreads the atomics of a small batch (a caller may bring 2n
-    // floats only)
-    const int slots = spread && n <= 32 ? 32 / n : 1;
-    fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws), 2 * n * slots, 0u);
-    if (items < kRedSmallItems)
-        minmax_kernel<B, 256><<<dim3(grid_x(items, 64, n, kRedGrid), n), 256, 0, st>>>(x, E, ws, slots);
-    else
-        minmax_kernel<B, red_threads<B>><<<dim3(grid_x(items, red_threads<B> / 4, n, kRedGrid), n), red_threads<B>, 0, st>>>(x, E, ws, slots);
+    fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(ws), 2 * n, 0u);
+    red_launch<B>(n, items, red_mapped<B>(n, E), [&](auto rt, auto u, auto fwd, int blocks) {
+        constexpr int RT = decltype(rt)::value;
+        minmax_kernel<B, RT, decltype(u)::value, decltype(fwd)::value><<<dim3(blocks, n), RT, 0, st>>>(x, E, ws);
+    });
     quant_affine_kernel<B><<<dim3(grid_x(items, kQuadsPerBlock, n), n), kThreads, 0, st>>>(x, E, ws, xq, act_scale,
-                                                                                          act_zero, slots);
+                                                                                          act_zero);
     return hipGetLastError();
 }
 
@@ -614,18 +668,17 @@ hipError_t launch_affine_b(const float *x, int n, int64_t E, float *ws, int8_t *
 hipError_t launch_act_quant_affine(const float *x, int n, int64_t E, int hblock, float *ws, int8_t *xq,
                                    float *act_scale, int32_t *act_zero, hipStream_t st) {
     if (E % 4 != 0) return hipErrorInvalidValue;
-    const bool spread = (hblock & kAffineSpread) != 0;
-    switch (hblock & ~kAffineSpread) {
-        case 1: return launch_affine_b<1>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 2: return launch_affine_b<2>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 4: return launch_affine_b<4>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 8: return launch_affine_b<8>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 16: return launch_affine_b<16>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 32: return launch_affine_b<32>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 64: return launch_affine_b<64>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 128: return launch_affine_b<128>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 192: return launch_affine_b<192>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
-        case 320: return launch_affine_b<320>(x, n, E, ws, xq, act_scale, act_zero, spread, st);
+    switch (hblock) {
+        case 1: return launch_affine_b<1>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 2: return launch_affine_b<2>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 4: return launch_affine_b<4>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 8: return launch_affine_b<8>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 16: return launch_affine_b<16>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 32: return launch_affine_b<32>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 64: return launch_affine_b<64>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 128: return launch_affine_b<128>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 192: return launch_affine_b<192>(x, n, E, ws, xq, act_scale, act_zero, st);
+        case 320: return launch_affine_b<320>(x, n, E, ws, xq, act_scale, act_zero, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -530,7 +530,6 @@ int32_t hatq_fwht_quant_act_affine(const float *x, int32_t n, int32_t h, int32_t
     if (elems(n, h, w, c) < 0) return HATQ_EINVAL;
     const int64_t E = (int64_t)h * w * c;
     if (c % hblock != 0 || E % 4 != 0) return HATQ_EUNSUPPORTED;
-    if (ws_bytes >= hatq_fwht_quant_affine_ws_bytes(n)) hblock |= hatq::kAffineSpread;
     return hip_status(hatq::launch_act_quant_affine(x, n, E, hblock, static_cast<float *>(ws), xq, act_scale,
                                                     act_zero, static_cast<hipStream_t>(stream)));
 }

@@ -27,9 +27,6 @@ hipError_t launch_act_quant_noalloc(const float *x, int n, int64_t E, int hblock
 // Affine activation quantization (signed grid [-128, 127]) of n samples of E
 // floats each (E % 4 == 0, the channel count a multiple of hblock): ws holds 2n
 // floats (per-sample max(S, 0), then max(-S, 0)); per-sample scale and zero point out.
-// hblock | kAffineSpread: ws holds 2n floats rounded up to 64, and a small batch
-// spreads its maxima over them.
-constexpr int kAffineSpread = 1 << 16;
 hipError_t launch_act_quant_affine(const float *x, int n, int64_t E, int hblock, float *ws, int8_t *xq,
                                    float *act_scale, int32_t *act_zero, hipStream_t st);
 

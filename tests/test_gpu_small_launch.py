@@ -162,15 +162,15 @@ def test_reduction_block_sizes(shape, b):
     assert bool((qa.amax(dim=(1, 2, 3)) >= 126).all()) and bool((qa.amin(dim=(1, 2, 3)) <= -127).all())
 
 
-# The transformed maxima of the large-block reductions, exactly: small whole numbers
-# (every partial sum of the transform is exact in fp32), the transform a float64
-# product by the order's matrix, samples of more than 16384 items (blocks of 1024
-# threads, 512 for the order 320) and of fewer, and the largest positive and negative
-# values in the first item, the last and one in between.
-@pytest.mark.parametrize("b,pixels", [(16, 4133), (64, 16801), (128, 17419), (192, 16567), (320, 16453),
-                                      (64, 5003), (128, 1201), (192, 2503), (320, 907)])
-@pytest.mark.parametrize("n", [1, 3])
-def test_reductions_transformed(orc, b, pixels, n):
+# The transformed maxima of the reductions, exactly: small whole numbers (every
+# partial sum of the transform is exact in fp32), the transform a float64 product by the
+# order's matrix, samples on both sides of each limit of the launch shapes (threads,
+# blocks, own slots, forward order, one item per quad), and the largest positive and
+# negative values in the first item, the last and one in between.
+@pytest.mark.parametrize("n,b,pixels", [(n, b, p) for n in (1, 3) for b, p in (
+    (16, 4133), (64, 16801), (128, 17419), (192, 16567), (320, 16453), (64, 5003), (128, 1201), (192, 2503), (320, 907))]
+    + [(1, 64, 67), (2, 128, 6007), (2, 192, 1511), (17, 320, 2203), (131, 64, 2503), (131, 128, 4201)])
+def test_reductions_transformed(orc, n, b, pixels):
     c = 64 * 5 if b == 16 else b
     H = torch.from_numpy(orc.activation_transform(np.eye(b, dtype=np.float32).reshape(1, 1, b, b), b)
                          .reshape(b, b).astype(np.float64)).cuda()   # row i: the transform of unit vector i
