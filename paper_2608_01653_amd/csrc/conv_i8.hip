@@ -4117,7 +4117,8 @@ hipError_t conv_part_win_wide(const ConvArgs &a, bool *hit, hipStream_t st) {
 //    19/20/18, 1590 11/19/16, 2880 16/30/23 at 192 and 320 columns; the other
 //    widths, whose general kernel has run-time epilogues only, fp32 with maxima b8 288
 //    18/18/15, 384 21/18/15, 1536 43/38/30; accumulators 64 -> 448 224 6/7/8, 588
-//    13/16/15, 128 -> 448 2800 36/51/40, 192 -> 448 1008 21/22/17.
+//    13/16/15, 128 -> 448 2800 36/51/40, 192 -> 448 1008 21/22/17; integer codes 64 -> 128
+//    4800 41/-/52, 128 -> 128 6912 65/-/77, 192 -> 256 17472 385/-/350.
 static int win_rows(const ConvArgs *p, int nph) {
     const ConvArgs &a = p[0];
     if (a.cin_p % 64 || a.cout_pad % 64 || a.sa > 2) return 0;
@@ -4145,7 +4146,8 @@ static int win_rows(const ConvArgs *p, int nph) {
     if (b4 <= (a.ntaps > 1 ? 500 : nph > 1 ? 800 : 512)) return 4;
     if (nph > 1 || a.ntaps > 1) return 8;
     if (wide) return b4 <= 800 ? 8 : 0;
-    return a.mode == 0 && a.cin_p <= 128 && tile64 && b8 > 300 ? 0 : 8;
+    const int most = tile64 ? a.mode == 0 ? 300 : INT32_MAX : a.mode == kModeIntTransition ? 4000 : INT32_MAX;
+    return a.cin_p <= 128 && b8 > most ? 0 : 8;
 }
 
 // Whether conv_cols_kernel takes the launch: stride 1 and transposed, at least
