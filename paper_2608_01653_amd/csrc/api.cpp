@@ -254,8 +254,7 @@ int32_t conv_launches(const hatq_weights *W, const int8_t *xq, const float *sx, 
             }
         a.nksteps = small ? W->pack_stride / 64 : a.ntaps * (W->cin_pad / 64);
         a.M = (int64_t)n * a.gh * a.gw;
-        a.nph = 1;
-        return hip_status(hatq::launch_conv(a, true, st));
+        return hip_status(hatq::launch_conv(&a, 1, st));
     }
     // transposed, stride 2: four phases
     hatq::ConvArgs phases[hatq::kMaxPhases];
@@ -290,9 +289,7 @@ int32_t conv_launches(const hatq_weights *W, const int8_t *xq, const float *sx, 
             if (nt == 0) continue;   // cannot happen for k >= 2
             ++nph;
         }
-    if (nph == 0) return HATQ_OK;
-    phases[0].nph = nph;
-    return hip_status(hatq::launch_conv(phases[0], true, st));
+    return nph == 0 ? HATQ_OK : hip_status(hatq::launch_conv(phases, nph, st));
 }
 
 }  // namespace

@@ -3572,24 +3572,23 @@ __global__ void __launch_bounds__(64 * KS, MINB) conv_win_kernel(const WinArgs<W
 // loads the window once for all columns and phases.  At (4, 127, 95) transposed
 // 192 -> 192 a unit has 12-27 steps: divided over four waves, the partial sums,
 // the window and the block's start cost four times the products.
-template <int SA>
 struct ColsShape {
     static constexpr int MAXCOLS = 320;
-    static constexpr int BASE = WinShape<SA>::TAB * 8 + MAXCOLS * 8 + 512;   // step table, column factors, maximum
+    static constexpr int BASE = WinShape<1>::TAB * 8 + MAXCOLS * 8 + 512;   // step table, column factors, maximum
     static_assert(BASE % 512 == 0, "swizzle bits");
 };
-template <int FM, int SA, int LDSB, int MINB, typename E>
-__global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs<WinShape<SA>::NPH> wa) {
-    using W = WinShape<SA>;
-    constexpr int FN = 4, BN = 64, TW = W::TW, BASE = ColsShape<SA>::BASE;
+template <int FM, int LDSB, int MINB, typename E>
+__global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs<kMaxPhases> wa) {
+    using W = WinShape<1>;
+    constexpr int FN = 4, BN = 64, TW = W::TW, BASE = ColsShape::BASE;
     __shared__ __attribute__((aligned(1024))) int8_t lds[LDSB];
     uint2 *const s_tab = reinterpret_cast<uint2 *>(lds);   // step -> (window offset, weight offset), phase after phase
     float *const s_col = reinterpret_cast<float *>(lds + W::TAB * 8);
-    uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_col + 2 * ColsShape<SA>::MAXCOLS);
+    uint32_t *const s_max = reinterpret_cast<uint32_t *>(s_col + 2 * ColsShape::MAXCOLS);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-    const int nph = W::NPH == 1 ? 1 : (int)wa.nph.d, tn = (int)wa.tiles_n.d;
+    const int nph = (int)wa.nph.d, tn = (int)wa.tiles_n.d;
     const ConvArgs &a0 = wa.p[0];
     const int l0 = xcd_logical_tile();
     Tile tile;
@@ -3606,21 +3605,19 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
     // the window (of all phases)
     const int rows = wa.g[0].rows, cols = wa.g[0].cols, nblk = W::chunk_blocks(rows), chunk_b = nblk * 1024;
     {
-        const uint32_t px = a0.xq_c64 ? 64u : (uint32_t)cin_p;
-        const uint32_t chunk_stride = a0.xq_c64 ? (uint32_t)(a0.h * a0.w * 64) : 64u;
+        // (NHWC codes: chunk-major ones are for the 5x5 stride-2 layers)
         const uint32_t sample = (uint32_t)(tile.nb * a0.h * a0.w) * (uint32_t)cin_p;
-        const int ih0 = tile.gi0 * SA + wa.g[0].h0, iw0 = tile.gj0 * SA + wa.g[0].w0;
+        const int ih0 = tile.gi0 + wa.g[0].h0, iw0 = tile.gj0 + wa.g[0].w0;
         for (int b = wave; b < nblk; b += nw) {
             const int f = 16 * b + (lane >> 2);
             const int g = (lane & 3) ^ swz(f);
-            const int row = f / W::RR, rem = f - row * W::RR;
-            const int col = SA == 2 ? (rem < W::HCC ? 2 * rem : 2 * (rem - W::HCC) + 1) : rem;
+            const int row = f / W::RR, col = f - row * W::RR;
             const int ih = ih0 + row, iw = iw0 + col;
             const bool in = (row < rows) & (col < cols) & ((unsigned)ih < (unsigned)a0.h) &
                             ((unsigned)iw < (unsigned)a0.w);
-            const uint32_t off = in ? sample + (uint32_t)(ih * a0.w + iw) * px + 16u * g : kOobOffset;
+            const uint32_t off = in ? sample + (uint32_t)(ih * a0.w + iw) * (uint32_t)cin_p + 16u * g : kOobOffset;
             for (int c = 0; c < nchunks; ++c)
-                dma16s(rx, lds + BASE + c * chunk_b + b * 1024, off, (uint32_t)c * chunk_stride);
+                dma16s(rx, lds + BASE + c * chunk_b + b * 1024, off, (uint32_t)c * 64u);
         }
     }
     for (int ph = 0, base = 0; ph < nph; ++ph) {
@@ -3630,7 +3627,7 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
             const int c = wg.ntaps.div(s), t = s - c * ntaps;
             const int i = wg.nkw.div(t), j = t - i * (int)wg.nkw.d;
             const int r = wg.r0 + i * wg.ri, q = wg.c0 + j * wg.cj;
-            const int rec = r * W::RR + (SA == 2 ? (q & 1) * W::HCC + (q >> 1) : q);
+            const int rec = r * W::RR + q;
             const int wt = wg.t0 + i * wg.ti + j * wg.tj;
             s_tab[base + s] = make_uint2((uint32_t)(c * chunk_b + rec * 64),
                                          (uint32_t)((wt * nchunks + c) * a0.cout_pad) * 64u);
@@ -3639,7 +3636,7 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
     }
     const float sxv = tile_sx(a0, tile.nb);
     for (int c = tid; c < tn * BN; c += blockDim.x)
-        column_factor(a0, sxv, c, s_col[c], s_col[ColsShape<SA>::MAXCOLS + c]);
+        column_factor(a0, sxv, c, s_col[c], s_col[ColsShape::MAXCOLS + c]);
     if (tid == 0) *s_max = 0;
     wait_vmcnt<0>();
     __syncthreads();
@@ -3650,9 +3647,9 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
     // the next so that each wave has long and short ones
     const int units = tn * nph;
     for (int u = wave; u < units; u += nw) {
-        const int cg = W::NPH == 1 ? u : wa.nph.div(u);
-        int ph = W::NPH == 1 ? 0 : u - cg * nph + cg;
-        if (W::NPH > 1) ph -= wa.nph.div(ph) * nph;
+        const int cg = wa.nph.div(u);
+        int ph = u - cg * nph + cg;
+        ph -= wa.nph.div(ph) * nph;
         const ConvArgs &a = wa.p[ph];
         const int nks = (int)wa.g[ph].ntaps.d * nchunks;
         const uint2 *tab = s_tab;
@@ -3697,7 +3694,7 @@ __global__ void __launch_bounds__(kThreads, MINB) conv_cols_kernel(const WinArgs
             });
         }
         epilogue_regs<TW, FM, FN, E>(a, acc, tile, 0, lane, s_col + tile.n0,
-                                     s_col + ColsShape<SA>::MAXCOLS + tile.n0, s_max);
+                                     s_col + ColsShape::MAXCOLS + tile.n0, s_max);
     }
     if (EpiFlags<E>(a0).want_abs) {
         __syncthreads();
@@ -3781,11 +3778,10 @@ int64_t win_blocks(const A &w) {
 
 // The same for conv_cols_kernel: one window over all phases, every chunk of it in
 // LDS, the table of all phases, 64-column groups up to 320 columns.
-template <int SA>
-bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA>::NPH> *w) {
-    using W = WinShape<SA>;
-    using C = ColsShape<SA>;
-    if (!win_args<SA>(p, nph, FM, 64, LDSB, w)) return false;
+inline bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<kMaxPhases> *w) {
+    using W = WinShape<1>;
+    using C = ColsShape;
+    if (!win_args<1>(p, nph, FM, 64, LDSB, w)) return false;
     int h0 = w->g[0].h0, w0 = w->g[0].w0, h1 = h0, w1 = w0, steps = 0;   // first and one past the last row and column
     for (int i = 0; i < nph; ++i) {
         const WinGeom &g = w->g[i];
@@ -3806,7 +3802,6 @@ bool cols_args(const ConvArgs *p, int nph, int FM, int LDSB, WinArgs<WinShape<SA
         g.w0 = w0;
         g.rows = rows;
         g.cols = cols;
-        g.nbuf = nchunks;
     }
     return true;
 }
@@ -3916,16 +3911,16 @@ hipError_t try_epilogue(const ConvArgs &a, bool *hit, L &&launch) {
     return r;
 }
 
-template <int FM, int SA, int LDSB, int MINB>
+template <int FM, int LDSB, int MINB>
 hipError_t launch_cols(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
-    WinArgs<WinShape<SA>::NPH> w;
-    *hit = cols_args<SA>(p, nph, FM, LDSB, &w);
+    WinArgs<kMaxPhases> w;
+    *hit = cols_args(p, nph, FM, LDSB, &w);
     if (!*hit) return hipSuccess;
     const int64_t blocks = (int64_t)w.p[0].n * w.per.d, units = (int64_t)w.tiles_n.d * w.nph.d;
     const int waves = units < 4 ? (int)units : 4;
     // (the run-time epilogues, which spill here, stay with conv_win_kernel)
     return try_epilogue<HATQ_WIN_FIXED>(p[0], hit, [&](auto e) {
-        conv_cols_kernel<FM, SA, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * waves, 0, st>>>(w);
+        conv_cols_kernel<FM, LDSB, MINB, decltype(e)><<<(unsigned)blocks, 64 * waves, 0, st>>>(w);
         return hipGetLastError();
     });
 }
@@ -4081,7 +4076,7 @@ hipError_t conv_part_win1(const ConvArgs *p, int nph, int fm, bool *hit, hipStre
 
 #if HATQ_PART(16)
 hipError_t conv_part_cols1(const ConvArgs *p, int nph, bool *hit, hipStream_t st) {
-    return launch_cols<8, 1, 81920, 2>(p, nph, hit, st);
+    return launch_cols<8, 81920, 2>(p, nph, hit, st);
 }
 #endif
 
@@ -4216,11 +4211,10 @@ static hipError_t launch_conv_one(const ConvArgs &a, hipStream_t st) {
         default: return conv_part_pipe_other(a, st);
     }
 }
-hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st) {
-    const ConvArgs *const p = &a;
-    const int nph = a.nph;
+hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st) {
     if (nph < 1 || nph > kMaxPhases) return hipErrorInvalidValue;
-    if (clear_next && a.next_absmax && a.next_hblock > 0)
+    const ConvArgs &a = p[0];
+    if (a.next_absmax && a.next_hblock > 0)
         fill_u32_kernel<<<1, 256, 0, st>>>(reinterpret_cast<uint32_t *>(a.next_absmax), a.n, 0u);
     if (wide_rows(p, nph)) {
         bool hit = false;

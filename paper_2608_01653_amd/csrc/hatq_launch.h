@@ -83,16 +83,14 @@ struct ConvArgs {
     int32_t tiles_h, tiles_w, tiles_n;   // 2-D tiles of grid points per sample; column tiles
     int32_t n_base;        // first output column of a launch over a column range, else 0
     int32_t run_tiles;     // row-run kernel: tiles per block (set at launch)
-    int32_t nph;           // phases of this convolution (launch_conv)
     int8_t dh[kMaxTaps], dw[kMaxTaps];
     int16_t wtap[kMaxTaps];
 };
 
-// One convolution: a and, for the phases of a transposed one, the a.nph - 1
-// ConvArgs that follow it in memory (the same tensors).  clear_next: zero
-// next_absmax first (it collects all phases).
+// One convolution: p[0], or the nph phases of a transposed one (the same tensors).
+// Zeroes next_absmax first (it collects all phases).
 constexpr int kMaxPhases = 4;
-hipError_t launch_conv(const ConvArgs &a, bool clear_next, hipStream_t st);
+hipError_t launch_conv(const ConvArgs *p, int nph, hipStream_t st);
 
 // Weight preparation: transform, per-channel scale, codes, bias.
 struct PrepArgs {
