@@ -1190,11 +1190,10 @@ struct Epilogue {
     __device__ __forceinline__ void finish() {
         if (fl.want_abs) {
             const float m = wave_max(wave_m);
-            // With a slot the block publishes once for all its waves (device-scope
-            // atomics on one address take some 7 ns each, one after the other).
-            // The running maximum only grows, so a wave whose maximum does not exceed
-            // a value already published skips its atomic.  Device-scope atomics on
-            // one address serialize, and most waves of a layer end up skipping.
+            // With a slot the block publishes once for all its waves: device-scope atomics
+            // on one address take some 7 ns each, one after the other.  Without, a wave
+            // whose maximum does not exceed a value already published skips its atomic
+            // (the running maximum only grows; most waves of a layer skip).
             if (slot != nullptr) {
                 if (lane == 0)
                     __hip_atomic_fetch_max(slot, __float_as_uint(m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -176,12 +176,18 @@ def _nhwc(t: torch.Tensor, name: str, dtype: torch.dtype, channels: Optional[int
     return shape
 
 
+# (a private name of torch: where a version lacks it, the public call, 1-2 us slower)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
     """The raw stream handle: the given stream's, or that of the current stream of
     the current device."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def desc(cin, cout, k, stride, pad, hblock, transposed=False, out_pad=0) -> ConvDesc:

@@ -332,3 +332,15 @@ def test_layer_forward_form_flag_and_workspace(L):
              None) == hatq.HATQ_EWORKSPACE
     assert f(ctypes.byref(W), 0, FAKE, 1, 16, 16, None, FAKE, None, 0, None, None, need,
              None) == hatq.HATQ_EINVAL
+
+
+def test_stream_without_the_private_call(monkeypatch):
+    """The binding's raw stream handle comes from torch's public call where its private
+    one is missing; a given stream is used as it is."""
+    class S:
+        cuda_stream = 4711
+    monkeypatch.setattr(hatq, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: S)
+    assert hatq._stream() == 4711
+    S2 = type("S2", (), {"cuda_stream": 12})
+    assert hatq._stream(S2) == 12
