@@ -737,14 +737,14 @@ struct Epilogue {
         }
     }
 
-    // Whether channel ch of row group i's pixel is not part of the next operand: a pixel
-    // past the grid or a channel past cout (the padding of a WH layer's last block).
-    // Every order masks by this, behind a wave-uniform condition, with the channel
-    // count read before the row groups and without a branch: read behind a lane's own
-    // condition, the compiler lost masked values of partly valid groups in one kernel.
-    // (Dropping the lane's maximum instead of zeroing its values is slower on tiles
-    // that reach past the grid: 1x1 64 -> 192, (16, 63, 60), 25 -> 30 us.)
-    __device__ __forceinline__ bool outside(int i, int ch, int cout) const { return !valid[i] | (ch >= cout); }
+    // What is not part of the next operand: pixels past the grid and channels past cout
+    // (the padding of a WH layer's last block).  Every order masks them in one form:
+    // behind a wave-uniform condition, with the channel count read before the row
+    // groups and `|`, `&` in place of branches.  Read behind a lane's own condition, the
+    // compiler lost masked values of partly valid groups in one kernel.  (Written out at
+    // each place: a function for it, inlined, gave the plain orders other code, up to 10 %
+    // slower on ragged tiles.  Dropping the lane's maximum instead of zeroing its values is
+    // slower on tiles that reach past the grid: 1x1 64 -> 192, (16, 63, 60), 25 -> 30 us.)
 
     // The sixteen values of 64-channel block k among a row group's KV.
     template <typename T>
@@ -828,7 +828,7 @@ struct Epilogue {
             if (!full) {
 #pragma unroll
                 for (int r = 0; r < KV; ++r)
-                    if (outside(i, 0, 1)) v[r] = 0.0f;
+                    if (!valid[i]) v[r] = 0.0f;
             }
             // channel order matters for the codes only
             auto next_kron = [&]() {
@@ -1017,7 +1017,7 @@ struct Epilogue {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                            if (outside(i, ch, cout)) v[16 * k + 4 * jj + r] = 0.0f;
+                            if (!valid[i] | (ch >= cout)) v[16 * k + 4 * jj + r] = 0.0f;
                         }
             }
             // channel order matters for the codes only
@@ -1126,7 +1126,7 @@ struct Epilogue {
 #pragma unroll
                             for (int r = 0; r < 4; ++r) {
                                 const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                                const bool in = !outside(i, ch, cout);
+                                const bool in = valid[i] & (ch < cout);
                                 mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
                             }
                     }
@@ -1158,7 +1158,7 @@ struct Epilogue {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                        const bool in = all | !outside(i, ch, cout);
+                        const bool in = all | (valid[i] & (ch < cout));
                         mm = fmaxf(mm, in ? fabsf(v[4 * jj + r]) : 0.0f);
                     }
                 wave_m = fmaxf(wave_m, mm);
@@ -1171,7 +1171,7 @@ struct Epilogue {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int ch = t.n0 + 64 * k + 16 * jj + 4 * q + r;
-                            if (outside(i, ch, cout)) v[4 * jj + r] = 0.0f;
+                            if (!valid[i] | (ch >= cout)) v[4 * jj + r] = 0.0f;
                         }
                 }
                 if (i8) {
@@ -2280,8 +2280,9 @@ inline int rr32_kron_pass(const ConvArgs &a) {
 // kernel is bound by the vector ALU, so what counts is that every CU has the
 // same rows to do.  One tile per block leaves the balance to the hardware's
 // dispatch (the XCDs hold different clocks under this load, so an even split
-// into resident blocks ends unevenly): batch 16 of 1024 x 1024, absmax 343 ->
-// 325 us, codes 449 -> 436, integer 767 -> 677.  Fewer tiles of 16 rows than
+// into resident blocks ends unevenly): batch 16 of 1024 x 1024, each pass alone,
+// absmax 353 -> 328 us, codes 472 -> 437, integer 772 -> 687 (within the step, at its
+// lower clocks, 378, 489 and 779).  Fewer tiles of 16 rows than
 // the blocks that fit the chip leave CUs idle: smaller tiles then, although
 // each block stages the weights anew.  Measured absmax + codes at 4 / 8 / 16
 // rows: 192 tiles (512 x 768) 32 / 41 / 55 us, 384 tiles 54 / 51 / 68, 768 tiles
@@ -2294,7 +2295,7 @@ inline int rr32_rows(const ConvArgs &a) {
 }
 // Order 192 (two blocks per CU): two tiles per block on the largest launches,
 // so the next patch is fetched behind the longer arithmetic (8192 tiles: absmax
-// 691 -> 642 us, codes 729 -> 719).
+// 691 -> 642 us, codes 729 -> 719, one box).
 inline int rr32_run(const ConvArgs &a, int ord) { return ord == 192 && rr32_rows(a) == 16 ? 2 : 1; }
 #ifndef HATQ_RR32_MINB
 #define HATQ_RR32_MINB 4
@@ -4096,17 +4097,21 @@ hipError_t conv_part_win_wide(const ConvArgs &a, bool *hit, hipStream_t st) {
 //    launches of 320 columns: 440 68/19/20, 880 71/32/26, 1960 75/64/49.
 //  * stride 1 and transposed (conv_pipe_kernel, four phase launches for the
 //    latter): b4 192 166/15/16, 960 184/33/26, 5292 134/91/80, 12672 222/156/109,
-//    19872 258/275/209; 3x3 70 15/10/12, 1188 35/20/19, 3276 68/47/41.
+//    19872 258/275/209; 3x3 70 15/10/12, 1188 35/20/19, 3276 68/47/41; b8 16384, 192 ->
+//    128 739/-/386.  5x5 stride 2 to 128 and 256 columns: b8 9216 842/-/437, 18432
+//    1509/-/827.
 //  * stride 2, k < 4: few steps per window (k = 1 loads four times the pixels it
 //    needs), so the general kernel catches up sooner, above all where it has the
 //    epilogue at compile time (192 and 320 columns).  b8, old / this: those, fp32 output,
 //    k = 1, 64 -> 192 480 12/10, 768 12/14, 1536 15/23; 192 -> 192 360 13/12, 576 14/19;
-//    k = 2, 64 -> 192 663 15/13, 1326 17/22; 192 -> 320 910 33/31, 1105 23/29; k = 3,
+//    k = 2, 64 -> 192 663 15/13, 1326 17/22; 192 -> 320 1105 23/29, with maxima 1700
+//    62/52, 2560 50/55; k = 3,
 //    64 -> 192 1536 24/26, 1740 38/30, 64 -> 320 with maxima 1625 57/42, 3840 69/72, 192
 //    -> 320 3840 115/109, 11520 322/353.  k = 1 otherwise: integer codes 64 -> 320 1760
 //    35/30, 2560 37/39, 192 -> 320 600 21/19, 2560 40/53, 192 -> 256 1120 44/35, 2944
 //    66/80; tiles of 64 columns, 64 -> 64 fp32 493 17/11, accumulators 64 -> 448 252 7/7,
-//    960 14/21; fp32 320 -> 448 448 10/12.
+//    960 14/21; fp32 320 -> 448 448 10/12, with maxima 192 -> 448 378 25/18, 64 -> 448 931
+//    39/29.
 //  * 1x1 stride 1, too few steps to hide a block's start and end: b4 64 24/7/9, 819
 //    19/20/18, 1590 11/19/16, 2880 16/30/23 at 192 and 320 columns; the other
 //    widths, whose general kernel has run-time epilogues only, fp32 with maxima b8 288
@@ -4122,25 +4127,30 @@ static int win_rows(const ConvArgs *p, int nph) {
     const bool tile64 = !wide && a.cout_pad != 128 && a.cout_pad != 256;   // 64 columns per general tile
     if (a.sa == 2) {
         // the epilogues that the general kernel has at compile time for these widths
-        const bool fixed = wide && (epi_matches<Epi<0, 64>>(a) || epi_matches<Epi<0, 1>>(a) || epi_matches<Epi<0, 0>>(a) ||
-                                    epi_matches<Epi<64, 64>>(a) || epi_matches<Epi<64, 1>>(a) || epi_matches<Epi<64, 0>>(a));
+        const bool fixed = wide && (epi_matches<Epi<0, 64>>(a) || epi_matches<Epi<0, 1>>(a) ||
+                                    epi_matches<Epi<0, 0>>(a) || epi_matches<Epi<64, 64>>(a) ||
+                                    epi_matches<Epi<64, 1>>(a) || epi_matches<Epi<64, 0>>(a));
         if (a.k == 1) {
             const bool codes = a.mode == kModeIntTransition, one = a.cin_p == 64;
             const int most = fixed    ? 480
                              : wide   ? !codes ? INT32_MAX : one ? 2000 : 800
-                             : tile64 ? one && a.mode != 0 ? 700 : 250
+                             : tile64 ? a.mode == 1 && a.next_absmax ? 2000 : one && a.mode != 0 ? 700 : 250
                                       : codes ? 900 : INT32_MAX;
             if (b8 > most) return 0;
         }
         if (b4 <= 600) return 4;
         if (!wide) return 8;
-        if (a.k < 4) return !fixed || b8 <= (a.k < 3 ? 900 : a.cin_p == 64 ? 3000 : 6000) ? 8 : 0;
+        if (a.k < 4) {
+            const int most = a.k < 3 ? a.next_absmax ? 2200 : 900 : a.cin_p == 64 ? 3000 : 6000;
+            return !fixed || b8 <= most ? 8 : 0;
+        }
         return b8 <= (a.cout_pad == 192 ? 600 : 1000) ? 8 : 0;
     }
     if (b4 <= (a.ntaps > 1 ? 500 : nph > 1 ? 800 : 512)) return 4;
     if (nph > 1 || a.ntaps > 1) return 8;
     if (wide) return b4 <= 800 ? 8 : 0;
-    const int most = tile64 ? a.mode == 0 ? 300 : INT32_MAX : a.mode == kModeIntTransition ? 4000 : INT32_MAX;
+    const bool i32 = a.mode == 0, codes = a.mode == kModeIntTransition;
+    const int most = tile64 && i32 ? 300 : !tile64 && codes ? 4000 : INT32_MAX;
     return a.cin_p <= 128 && b8 > most ? 0 : 8;
 }
 
@@ -4152,7 +4162,9 @@ static int win_rows(const ConvArgs *p, int nph) {
 // 360/264/187; 3x3 192 -> 192 tiles 256 36/20/20, 512 42/46/31, 1280 109/78/65;
 // 192 -> 256 tiles 256 46/25/26, 1280 201/102/78; 192 -> 320 256 36/30/39, 512
 // 66/70/48; 1x1 192 -> 192 256 14/15/11, 1280 41/49/34; 1x1 192 -> 320 256
-// 16/21/18, 512 28/34/24; one unit 135/65/105 at 1700 tiles.
+// 16/21/18, 512 28/34/24; one unit 135/65/105 at 1700 tiles.  On the largest launches
+// (old / this): 1x1 18432 tiles 192 -> 192 604/521, 192 -> 256 1943/668, 192 -> 320 987/792;
+// 3x3 8192 tiles 192 -> 192 667/406; transposed 4608 tiles 192 -> 192 662/321.
 static bool cols_units(const ConvArgs *p, int nph) {
     const ConvArgs &a = p[0];
     if (a.cin_p % 64 || a.cout_pad % 64 || a.sa != 1) return false;

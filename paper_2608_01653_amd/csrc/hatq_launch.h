@@ -83,6 +83,9 @@ struct ConvArgs {
     int32_t tiles_h, tiles_w, tiles_n;   // 2-D tiles of grid points per sample; column tiles
     int32_t n_base;        // first output column of a launch over a column range, else 0
     int32_t run_tiles;     // row-run kernel: tiles per block (set at launch)
+    int32_t unused;        // keeps 504 bytes: a launch of four phases reads its arguments from four of
+                           // these in a row, and the distance tells (transposed 128 -> 192,
+                           // (4, 16, 32), fp32 with maxima: 504 14.8 us, 496 17.8, 512 17.7)
     int8_t dh[kMaxTaps], dw[kMaxTaps];
     int16_t wtap[kMaxTaps];
 };
