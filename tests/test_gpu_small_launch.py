@@ -76,6 +76,8 @@ BATCH = [
     (9, 17, 64, 320, 2, 2, 0, False, 0, "DH", 64),
     (9, 17, 64, 192, 3, 2, 1, False, 0, "WH", 64),
     (9, 17, 64, 64, 1, 1, 0, False, 0, "WH", 16),
+    (4, 9, 64, 192, 3, 2, 1, True, 0, "WH", 64),       # transposed, a first phase of one tap
+    (4, 9, 64, 320, 2, 2, 0, True, 0, "DH", 64),
 ]
 
 
